@@ -158,6 +158,17 @@ __device__ __forceinline__ float pick(uint32_t mask, float a, float b) {
     return __uint_as_float((__float_as_uint(a) & ~mask) | (__float_as_uint(b) & mask));
 }
 
+// the value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ float swap_lane1(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+
+// element offset of token `tok`'s head 0 in a BHTD target layer
+__device__ __forceinline__ size_t bhtd_row(const Problem& p, int tok) {
+    const int b = tok / p.T, t = tok % p.T;
+    return ((size_t)b * p.H_tgt * p.T + t) * p.D_tgt;
+}
+
 __device__ __forceinline__ void wait_vm_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Compile-time loop: f(std::integral_constant<int, I>) for I in [B, E).
@@ -187,6 +198,9 @@ void k_bf16_fused(Problem p, UnitTab ut) {
     u32x4* Hs = smem + C::OFF_H;
     float* Gs = reinterpret_cast<float*>(smem + C::OFF_G);
     u32x4* Xs = smem + C::OFF_X;   // fp32 layer-1 results handed to wave 3
+    // routed tiles: the token of row r of block tb, in the gate row of
+    // translator 1 (a routed walk has translator 0's gates only)
+    int32_t* s_tok = reinterpret_cast<int32_t*>(Gs) + 32;
     // Translator usage of the tile (non-routed mode): MOT_MAX_EXPERTS
     // counters in the last 64 bytes of W1 stage 1, which holds the router
     // rows during the router and is zeroed there for rows >= E (these words
@@ -324,6 +338,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
                 const bool ok = ROUTED ? r < tile.z : tok0 + r < p.n_tok;
                 const int my_tok = ROUTED ? (ok ? p.rt.list[(size_t)unit_gslot(code) * p.n_tok * p.top_k + tile.y + r] : 0)
                                           : tok0 + r;
+                if (ROUTED && q4 == 0) s_tok[w * (MOT_MAX_EXPERTS * 32) + 16 * th + l16] = my_tok;
                 const int b = ok ? my_tok / p.T : 0, t = ok ? my_tok % p.T : 0;
 #pragma unroll
                 for (int s = 0; s < KS2; ++s) {
@@ -814,47 +829,54 @@ void k_bf16_fused(Problem p, UnitTab ut) {
         sync_stage();                                                   // c = nch + 1
         l2_iter(T, F, F, nch + 1, nch + 2, m1, kk1, w2_stage(nch + 1));
 
-        // epilogue: bf16 round and store in the target layout
-        {
+        // epilogue: bf16 round and store in the target layout.  A lane holds one
+        // column of rows 4g + (e & 3); neighbouring lanes exchange an element
+        // of two rows, so that the even lane stores both columns of the even
+        // row and the odd lane those of the odd row (4-byte stores, half as
+        // many, and one row address per pair instead of two).  The routed rows'
+        // tokens come from LDS: one dependent global read of the token list
+        // per row cost a tile ~1/8 of its time (56 units x 4096 tokens, Top-1
+        // of 8, 256 -> 512: 1068 -> 958 us per call)
         uint16_t* dst = reinterpret_cast<uint16_t*>(p.dst[x]) + (size_t)j * p.n_tok * D_OUT;
+        const bool odd_lane = lane & 1;
+        const bool to_part = ROUTED && p.top_k > 1;
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
+            if (to_part) {
+                // fp32 row of assignment tile.y + r; the combine sums a token's rows
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int r = tb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);   // row of the tile
-                int tok;
-                if constexpr (ROUTED) {
+                for (int e = 0; e < 16; ++e) {
+                    const int r = tb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
                     if (r >= tile.z) continue;
-                    const size_t NK = (size_t)p.n_tok * p.top_k;
-                    if (p.top_k > 1) {
-                        // fp32 row of assignment tile.y + r; the combine sums a token's rows
-                        float* prow = p.rt.part + (blockIdx.y * NK + tile.y + r) * D_OUT;
+                    float* prow = p.rt.part + (blockIdx.y * (size_t)p.n_tok * p.top_k + tile.y + r) * D_OUT;
 #pragma unroll
-                        for (int nb = 0; nb < C::NBW; ++nb)
-                            prow[q2 * C::OUTW + nb * 32 + l32] = acc[tb][nb][e];
-                        continue;
-                    }
-                    tok = p.rt.list[(size_t)unit_gslot(code) * NK + tile.y + r];
-                } else {
-                    tok = tok0 + r;
-                    if (tok >= p.n_tok) continue;
+                    for (int nb = 0; nb < C::NBW; ++nb) prow[q2 * C::OUTW + nb * 32 + l32] = acc[tb][nb][e];
                 }
-                const int b = tok / p.T, t = tok % p.T;
+                continue;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const int r = tb * 32 + 8 * (e >> 2) + 4 * g + (e & 3) + (odd_lane ? 1 : 0);   // row of the tile
+                const int tok = ROUTED ? s_tok[tb * (MOT_MAX_EXPERTS * 32) + (r & 31)] : tok0 + r;
+                const bool ok = ROUTED ? r < tile.z : tok < p.n_tok;
+                const size_t bt = p.dst_layout == MOT_LAYOUT_BTHD ? 0 : bhtd_row(p, tok);
 #pragma unroll
                 for (int nb = 0; nb < C::NBW; ++nb) {
-                    const int o = q2 * C::OUTW + nb * 32 + l32;
+                    const float a0 = acc[tb][nb][e], a1 = acc[tb][nb][e + 1];
+                    const float got = swap_lane1(odd_lane ? a0 : a1);
+                    const uint32_t v = pack_bf16x2(odd_lane ? got : a0, odd_lane ? a1 : got);
+                    const int o = q2 * C::OUTW + nb * 32 + (l32 & ~1);
                     size_t off;
                     if (p.dst_layout == MOT_LAYOUT_BTHD) {
                         off = (size_t)tok * D_OUT + o;
                     } else {
                         const int hh = o / p.D_tgt, dd = o % p.D_tgt;
-                        off = (((size_t)b * p.H_tgt + hh) * p.T + t) * p.D_tgt + dd;
+                        off = bt + (size_t)hh * p.T * p.D_tgt + dd;
                     }
-                    dst[off] = (uint16_t)(pack_bf16x2(acc[tb][nb][e], 0.f) & 0xFFFFu);
+                    if (ok) *reinterpret_cast<uint32_t*>(dst + off) = v;
                 }
             }
         }
-    }
     } else {
         // wave 3 when TB = 3: no token block; it helps stage the router
         // weights, then (NOFF > 0) evaluates the GELU of the row-half-1
