@@ -198,6 +198,30 @@ mot_status mot_translate(const void* src_k, const void* src_v, const int32_t* la
 size_t mot_workspace_bytes(const mot_shapes* shapes);
 
 /*
+ * mot_translate with optional scratch for the fused dense path, whose own need
+ * is zero.  A launch whose token tiles do not fill whole rounds of the chip (a
+ * short context above all) then cuts its last tiles along the expert-hidden
+ * axis over several workgroups each, which leave fp32 partial rows in
+ * `scratch` that a second kernel sums.  Same results up to the order of those
+ * fp32 sums.  scratch: device, 16-byte aligned, used by this call only (calls
+ * that overlap in time need their own), not overlapping a cache or weights;
+ * NULL, or fewer bytes than mot_translate_scratch_bytes: exactly
+ * mot_translate.  Other paths ignore it.
+ */
+mot_status mot_translate_scratch(const void* src_k, const void* src_v, const int32_t* layer_map,
+                                 const mot_translator_weights* tw, const mot_router_weights* rw,
+                                 void* dst_k, void* dst_v, const mot_shapes* shapes, void* scratch,
+                                 size_t scratch_bytes, hipStream_t stream);
+
+/*
+ * Scratch bytes with which mot_translate_scratch splits a call of these shapes
+ * over layer_map (host int32[L_tgt]); 0 when it would not (the tiles fill the
+ * chip, another path, or a splitting that would not pay) or when an argument
+ * is invalid.
+ */
+size_t mot_translate_scratch_bytes(const mot_shapes* shapes, const int32_t* layer_map);
+
+/*
  * Depth-ratio channel map (paper App. C.3, "Depth-Ratio Mapping"): target
  * layer j reads source layer floor(j * L_src / L_tgt), in exact integer
  * arithmetic.  out: host int32[L_tgt].

@@ -28,7 +28,7 @@ EXPORTED = ("mot_translate", "mot_workspace_bytes", "mot_depth_ratio_map", "mot_
             "mot_last_error", "mot_abi_version", "mot_restore_kv", "mot_topS_select",
             "mot_replay_attention", "mot_backbone_param_count", "mot_backbone_translate",
             "mot_usage_stats", "mot_replay_workspace_bytes", "mot_backbone_workspace_bytes",
-            "mot_replay_attention_noalloc")
+            "mot_replay_attention_noalloc", "mot_translate_scratch", "mot_translate_scratch_bytes")
 
 
 class MotError(RuntimeError):
@@ -143,6 +143,11 @@ def load_library():
         lib.mot_translate.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                       ctypes.POINTER(_TW), ctypes.POINTER(_RW), ctypes.c_void_p,
                                       ctypes.c_void_p, ctypes.POINTER(_Shapes), ctypes.c_void_p]
+        lib.mot_translate_scratch.restype = ctypes.c_int
+        lib.mot_translate_scratch.argtypes = lib.mot_translate.argtypes[:8] + [ctypes.c_void_p, ctypes.c_size_t,
+                                                                               ctypes.c_void_p]
+        lib.mot_translate_scratch_bytes.restype = ctypes.c_size_t
+        lib.mot_translate_scratch_bytes.argtypes = [ctypes.POINTER(_Shapes), ctypes.c_void_p]
         lib.mot_workspace_bytes.restype = ctypes.c_size_t
         lib.mot_workspace_bytes.argtypes = [ctypes.POINTER(_Shapes)]
         lib.mot_depth_ratio_map.restype = ctypes.c_int
@@ -235,6 +240,7 @@ def translate(src_k, src_v, layer_map: Sequence[int], w1, b1, w2, b2, wr, br, ds
     ``shapes.dtype`` (torch.float32 or torch.bfloat16).  ``usage``: optional
     int32 tensor [L_tgt][streams][E] of translator selection counts that the
     call adds to (the library treats it as uint32)."""
+    import numpy as np
     import torch
     want = torch.float32 if shapes.dtype == MOT_F32 else torch.bfloat16
     dev = torch.device("cuda", torch.cuda.current_device())
@@ -253,9 +259,25 @@ def translate(src_k, src_v, layer_map: Sequence[int], w1, b1, w2, b2, wr, br, ds
         ws_bytes = workspace.numel() * workspace.element_size()
     if usage is not None and (usage.device != dev or usage.dtype != torch.int32 or not usage.is_contiguous()):
         raise MotError(2, "usage must be a contiguous int32 tensor on %s" % dev)
-    stream = torch.cuda.current_stream().cuda_stream
-    translate_raw(src_k, src_v, layer_map, w1, b1, w2, b2, wr, br, dst_k, dst_v, shapes,
-                  stream=stream, workspace=workspace, workspace_bytes_=ws_bytes, usage=usage)
+    lib = load_library()
+    lm = np.ascontiguousarray(layer_map, dtype=np.int32)
+    c = shapes.c(_ptr(workspace), ws_bytes, _ptr(usage))
+    # scratch of the split fused path: allocated for this call on the current
+    # stream, so torch's allocator orders its reuse (under graph capture too);
+    # without room for it the call runs unsplit
+    scratch, n = None, 0
+    if shapes.dtype == MOT_BF16 and lm.size == shapes.L_tgt:
+        n = lib.mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+        if n:
+            try:
+                scratch = torch.empty(n, dtype=torch.uint8, device=dev)
+            except torch.cuda.OutOfMemoryError:
+                n = 0
+    tw = _TW(_ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2))
+    rw = _RW(_ptr(wr), _ptr(br))
+    _check(lib.mot_translate_scratch(_ptr(src_k), _ptr(src_v), lm.ctypes.data if lm.size else None,
+                                     ctypes.byref(tw), ctypes.byref(rw), _ptr(dst_k), _ptr(dst_v), ctypes.byref(c),
+                                     _ptr(scratch), n, torch.cuda.current_stream().cuda_stream))
 
 
 def usage_stats(counts, cv2, entropy) -> None:

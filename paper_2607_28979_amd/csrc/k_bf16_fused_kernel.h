@@ -180,15 +180,28 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-// ROUTED: the workgroup runs one tile of the routed path: up to BM
-// assignments (token, gate) of a single translator, gathered by token index;
-// the router is skipped (the gates come with the assignments) and the E*hidden
-// walk covers that translator's hidden only.
-template <int D_IN, int D_OUT, int ACT, bool ROUTED>
+// What a workgroup of the fused kernel runs
+enum FusedMode {
+    // one token tile over the whole E*hidden walk; grid (tiles, units)
+    kFusedDense,
+    // one tile of the routed path: up to BM assignments (token, gate) of a
+    // single translator, gathered by token index; the router is skipped (the
+    // gates come with the assignments) and the walk covers that translator's
+    // hidden only; grid (max tiles, units)
+    kFusedRouted,
+    // dense over a linear grid: the first p.sp.full tiles (units outer) as
+    // in kFusedDense, then p.sp.parts workgroups for each of the last
+    // p.sp.tail tiles, every one walking its share of E*hidden and leaving an
+    // fp32 partial tile in p.sp.part for k_split_combine
+    kFusedSplit,
+};
+
+template <int D_IN, int D_OUT, int ACT, FusedMode MODE>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * Cfg<D_IN, D_OUT>::NW, 64 * Cfg<D_IN, D_OUT>::NW)))
 void k_bf16_fused(Problem p, UnitTab ut) {
     using C = Cfg<D_IN, D_OUT>;
     constexpr int TB = C::TB;
+    constexpr bool ROUTED = MODE == kFusedRouted;
     // the layer-2 waves issue the global -> LDS weight loads
     constexpr int NLD = C::L2W;
     constexpr int W1_RL = C::W1_CH / (64 * NLD), W2_RL = C::W2_CH / (64 * NLD);
@@ -210,7 +223,21 @@ void k_bf16_fused(Problem p, UnitTab ut) {
     uint32_t* s_usage = reinterpret_cast<uint32_t*>(W1s + 2 * C::W1_CH) - MOT_MAX_EXPERTS;
     static_assert(C::W1_CH / C::CPR1 == 32 && C::CPR1 * 16 >= MOT_MAX_EXPERTS * 4, "usage counters in row 31");
 
-    const uint32_t code = ut.code[blockIdx.y];
+    // token tile, position of the unit in the launch, and (kFusedSplit) the
+    // share of the walk: part `part` of `parts`
+    int tx = blockIdx.x, uy = blockIdx.y, part = 0, parts = 1;
+    if constexpr (MODE == kFusedSplit) {
+        int t = blockIdx.x;
+        if (t >= p.sp.full) {
+            parts = p.sp.parts;
+            part = (t - p.sp.full) / p.sp.tail;
+            t -= part * p.sp.tail;
+        }
+        const int ntx = (p.n_tok + C::BM - 1) / C::BM;
+        uy = t / ntx;
+        tx = t % ntx;
+    }
+    const uint32_t code = ut.code[uy];
     const int j = unit_j(code), x = unit_x(code), i = unit_i(code);
     const size_t unit = (size_t)j * p.streams + x;
     // routed tile: {translator, first assignment, rows}; tiles beyond the
@@ -235,17 +262,26 @@ void k_bf16_fused(Problem p, UnitTab ut) {
     const int tid = w * 64 + lane;   // logical thread index
     const int g = lane >> 5, l32 = lane & 31;
     const uint32_t gmask = 0u - (uint32_t)g;   // all ones in the upper lane half
-    const int tok0 = blockIdx.x * C::BM;
+    const int tok0 = tx * C::BM;
+    // chunks c_lo .. c_lo + nch of the E*hidden walk (both even), starting in
+    // translator m_lo at hidden kk_lo
+    int c_lo = 0, nch = EH / 32;   // nch >= 2
+    if constexpr (MODE == kFusedSplit) {
+        c_lo = 2 * (part * (EH / 64) / parts);
+        nch = 2 * ((part + 1) * (EH / 64) / parts) - c_lo;
+    }
+    const int m_lo = MODE == kFusedSplit ? c_lo * 32 / hidden : 0;
+    const int kk_lo = MODE == kFusedSplit ? c_lo * 32 - m_lo * hidden : 0;
     const bool is_l1 = w < TB;                 // layer-1 + GELU wave of token block w
     const bool is_l2 = w >= 4;                 // layer-2 wave q = w - 4
     const int q2 = w - 4;                      // layer-2 column group
     const int lw = q2;                         // index among the loading waves
 
-    const uint16_t* W1u = reinterpret_cast<const uint16_t*>(p.w1) + um * hidden * D_IN;
+    const uint16_t* W1u = reinterpret_cast<const uint16_t*>(p.w1) + (um * hidden + c_lo * 32) * D_IN;
     const uint16_t* W2u = reinterpret_cast<const uint16_t*>(p.w2) + um * D_OUT * hidden;
     // layer-1 bias: without one, every lane reads the same 16 zero bytes
     // (chunk and lane strides 0), so no mask is needed at the use
-    const uint16_t* b1u = p.b1 ? reinterpret_cast<const uint16_t*>(p.b1) + um * hidden
+    const uint16_t* b1u = p.b1 ? reinterpret_cast<const uint16_t*>(p.b1) + um * hidden + c_lo * 32
                                : reinterpret_cast<const uint16_t*>(&kZero16);
     const int b1_cstride = p.b1 ? 32 : 0;
     const uint16_t* b2u = p.b2 ? reinterpret_cast<const uint16_t*>(p.b2) + um * D_OUT : nullptr;
@@ -269,7 +305,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
     const uint32_t w2_lane = (uint32_t)((t_ld >> 2) * hidden + ((t_ld & 3) ^ ((t_ld >> 4) & 3)) * 8) * 2u;
     // chunk c of W1 (round r) into stage st; the chunk base is wave-uniform,
     // so each load is a scalar base plus a per-lane offset
-    const rsrc_t w1buf = make_rsrc(W1u, (uint32_t)EH * D_IN * 2);
+    const rsrc_t w1buf = make_rsrc(W1u, (uint32_t)nch * 32 * D_IN * 2);
     const rsrc_t w2buf = make_rsrc(W2u, (uint32_t)EH * D_OUT * 2);
     auto load_w1_round = [&](int c, int st, int r, uint32_t lane_off) {
         const uint32_t soff = (uint32_t)(c * 32 * D_IN + w1_perm(r * RS) * D_IN) * 2u;
@@ -280,7 +316,6 @@ void k_bf16_fused(Problem p, UnitTab ut) {
         const uint32_t soff = (uint32_t)((m * D_OUT + 16 * NLD * r) * hidden + kk) * 2u;
         load_lds16(w2buf, w2_lane, soff, W2s + st * C::W2_CH + r * 64 * NLD + lw * 64);
     };
-    const int nch = EH / 32;   // >= 2
     // The three roles run the same number of workgroup barriers: two around
     // the router, then one per pipeline iteration c = 0 .. nch+1.  Iteration c
     // runs layer 1 of chunk c, the GELU of chunk c-1 and layer 2 of chunk c-2;
@@ -611,7 +646,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
             }
         };
 
-        int m1 = 0, kk1 = 0;
+        int m1 = m_lo, kk1 = kk_lo;
         u32x4 bcur, bnext = {0u, 0u, 0u, 0u};
         load_b1(0, bcur);
         f32x4 s_prev[2][2], s_new[2][2];
@@ -686,7 +721,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
         __syncthreads();                                     // barrier A
         __syncthreads();                                     // barrier B
         // the tile's translator usage, counted by the layer-1 waves' router
-        if (!ROUTED && p.usage && q2 == 0 && lane < E && s_usage[lane])
+        if (!ROUTED && p.usage && part == 0 && q2 == 0 && lane < E && s_usage[lane])
             atomicAdd(p.usage + unit * E + lane, s_usage[lane]);
         // accumulators seeded with sum_m g_m b2_m[o] on MFMA: A = gates of a
         // token block (k = translator), B = b2 (k = translator); gates split
@@ -700,7 +735,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
             for (int nb = 0; nb < C::NBW; ++nb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[tb][nb][e] = 0.f;
-        if (b2u) {
+        if (b2u && part == 0) {
             u32x4 bv[C::NBW];
 #pragma unroll
             for (int nb = 0; nb < C::NBW; ++nb) {
@@ -787,7 +822,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
 
         // (m1, kk1): translator and column offset of W2 chunk kw, the one
         // fetched in iteration c: kw = c with three W2 stages, else c - 1
-        int m1 = 0, kk1 = 0;
+        int m1 = m_lo, kk1 = kk_lo;
         const std::integral_constant<bool, true> T{};
         const std::integral_constant<bool, false> F{};
         auto advance = [&]() {
@@ -839,16 +874,20 @@ void k_bf16_fused(Problem p, UnitTab ut) {
         // of 8, 256 -> 512: 1068 -> 958 us per call)
         uint16_t* dst = reinterpret_cast<uint16_t*>(p.dst[x]) + (size_t)j * p.n_tok * D_OUT;
         const bool odd_lane = lane & 1;
-        const bool to_part = ROUTED && p.top_k > 1;
+        const bool to_part = MODE == kFusedSplit ? parts > 1 : ROUTED && p.top_k > 1;
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
             if (to_part) {
-                // fp32 row of assignment tile.y + r; the combine sums a token's rows
+                // fp32 row of assignment tile.y + r, or of the tail tile's share;
+                // the combine sums a token's rows
+                const int rows = ROUTED ? tile.z : p.n_tok - tok0;
+                float* pbase = ROUTED ? p.rt.part + (uy * (size_t)p.n_tok * p.top_k + tile.y) * D_OUT
+                                      : p.sp.part + (size_t)(blockIdx.x - p.sp.full) * C::BM * D_OUT;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int r = tb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-                    if (r >= tile.z) continue;
-                    float* prow = p.rt.part + (blockIdx.y * (size_t)p.n_tok * p.top_k + tile.y + r) * D_OUT;
+                    if (r >= rows) continue;
+                    float* prow = pbase + (size_t)r * D_OUT;
 #pragma unroll
                     for (int nb = 0; nb < C::NBW; ++nb) prow[q2 * C::OUTW + nb * 32 + l32] = acc[tb][nb][e];
                 }
@@ -888,7 +927,7 @@ void k_bf16_fused(Problem p, UnitTab ut) {
         __syncthreads();
         const int l16 = lane & 15, q4 = lane >> 4;
         constexpr int NX = C::NOFF / 4, TH_OFF = 2 - NX;
-        int m3 = 0, kk3 = 0;
+        int m3 = m_lo, kk3 = kk_lo;
         for (int c = 0; c <= nch + 1; ++c) {
             sync_stage();
             if (C::NOFF > 0 && c >= 1 && c <= nch) {
@@ -925,16 +964,17 @@ void k_bf16_fused(Problem p, UnitTab ut) {
     }
 }
 
-template <int D_IN, int D_OUT, bool ROUTED>
+template <int D_IN, int D_OUT, FusedMode MODE>
 hipError_t launch_t(const Problem& p, const UnitTab& ut, hipStream_t stream) {
     using C = Cfg<D_IN, D_OUT>;
-    dim3 grid(ROUTED ? p.rt.max_tiles : (p.n_tok + C::BM - 1) / C::BM, ut.n);
+    const int ntx = (p.n_tok + C::BM - 1) / C::BM;
+    const dim3 grid = MODE == kFusedSplit ? dim3(p.sp.full + p.sp.tail * p.sp.parts)
+                                          : dim3(MODE == kFusedRouted ? p.rt.max_tiles : ntx, ut.n);
     if (p.act == MOT_ACT_GELU)
-        hipLaunchKernelGGL((k_bf16_fused<D_IN, D_OUT, MOT_ACT_GELU, ROUTED>), grid, dim3(64 * C::NW), 0, stream, p,
-                           ut);
+        hipLaunchKernelGGL((k_bf16_fused<D_IN, D_OUT, MOT_ACT_GELU, MODE>), grid, dim3(64 * C::NW), 0, stream, p, ut);
     else
-        hipLaunchKernelGGL((k_bf16_fused<D_IN, D_OUT, MOT_ACT_IDENTITY, ROUTED>), grid, dim3(64 * C::NW), 0, stream,
-                           p, ut);
+        hipLaunchKernelGGL((k_bf16_fused<D_IN, D_OUT, MOT_ACT_IDENTITY, MODE>), grid, dim3(64 * C::NW), 0, stream, p,
+                           ut);
     return hipGetLastError();
 }
 

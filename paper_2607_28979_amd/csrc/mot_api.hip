@@ -266,9 +266,26 @@ size_t mot_workspace_bytes(const mot_shapes* shapes) {
     return plan_bytes(pl, default_group(pl));
 }
 
+size_t mot_translate_scratch_bytes(const mot_shapes* s, const int32_t* layer_map) {
+    g_err[0] = 0;
+    if (check_shapes(s) != MOT_OK || !layer_map || (int64_t)s->B * s->T == 0) return 0;
+    static thread_local Plan pl;
+    make_plan(s, layer_map, &pl);
+    size_t bytes = 0;
+    if (pl.fused && !pl.routed) fused_split_plan(base_problem(s), pl.n_units, &bytes);
+    return bytes;
+}
+
 mot_status mot_translate(const void* src_k, const void* src_v, const int32_t* layer_map,
                          const mot_translator_weights* tw, const mot_router_weights* rw,
                          void* dst_k, void* dst_v, const mot_shapes* s, hipStream_t stream) {
+    return mot_translate_scratch(src_k, src_v, layer_map, tw, rw, dst_k, dst_v, s, nullptr, 0, stream);
+}
+
+mot_status mot_translate_scratch(const void* src_k, const void* src_v, const int32_t* layer_map,
+                                 const mot_translator_weights* tw, const mot_router_weights* rw,
+                                 void* dst_k, void* dst_v, const mot_shapes* s, void* scratch,
+                                 size_t scratch_bytes, hipStream_t stream) {
     g_err[0] = 0;
     mot_status st = check_shapes(s);
     if (st != MOT_OK) return st;
@@ -332,6 +349,14 @@ mot_status mot_translate(const void* src_k, const void* src_v, const int32_t* la
                 return fail(MOT_ERR_BAD_SHAPE, "workspace overlaps a destination cache");
         }
     }
+    if (scratch) {
+        if (!aligned16(scratch)) return fail(MOT_ERR_MISALIGNED, "scratch %p is not 16-byte aligned", scratch);
+        if (overlaps(scratch, scratch_bytes, dst_k, dst_bytes) ||
+            overlaps(scratch, scratch_bytes, src_k, src_bytes) ||
+            (two && (overlaps(scratch, scratch_bytes, dst_v, dst_bytes) ||
+                     overlaps(scratch, scratch_bytes, src_v, src_bytes))))
+            return fail(MOT_ERR_BAD_SHAPE, "scratch overlaps a cache");
+    }
     if (pl.n_units == 0 || n_tok == 0) return MOT_OK;   // nothing to translate
     if (need_min > 0 && !s->workspace) {
         st = owned_workspace(plan_bytes(pl, group), &ws);
@@ -388,6 +413,10 @@ mot_status mot_translate(const void* src_k, const void* src_v, const int32_t* la
     } else if (pl.fused) {
         ut.n = pl.n_units;
         memcpy(ut.code, pl.codes, sizeof(uint32_t) * pl.n_units);
+        size_t bytes = 0;
+        if (scratch) p.sp = fused_split_plan(p, pl.n_units, &bytes);
+        if (scratch_bytes < bytes) p.sp.parts = 1;
+        p.sp.part = reinterpret_cast<float*>(scratch);
         e = launch_bf16_fused(p, ut, stream);
     } else if (!pl.bf16 && f32_mfma_fits(p)) {
         for (int u0 = 0; e == hipSuccess && u0 < pl.n_units; u0 += group) {

@@ -44,6 +44,15 @@ struct Routing {
     int32_t tile_rows;  // assignments per tile
 };
 
+// Split of the fused dense path's last tiles (k_bf16_fused.hip): tiles of the
+// launch in order (units outer); parts <= 1: no split.
+struct FusedSplit {
+    float* part;        // [parts][tail][tile rows][d_out] fp32 partial tiles
+    int32_t full;       // tiles run by one workgroup each
+    int32_t tail;       // tiles after them, each run by `parts` workgroups
+    int32_t parts;
+};
+
 // Problem description handed to every kernel by value.
 struct Problem {
     const void* src[2];   // source K, V: [L_src] x layout
@@ -62,6 +71,7 @@ struct Problem {
     float* gates;         // workspace: [n_units_total][n_tok_pad][E] fp32
     void* hbuf;           // workspace: [group][n_tok_pad][E*hidden] (layout per path)
     Routing rt;           // routed path only
+    FusedSplit sp;        // fused dense path only
 };
 
 // Key/value restoration (MoT-h): K and V caches from a translated activation.
@@ -185,6 +195,9 @@ hipError_t launch_bf16_gemm2_routed(const Problem& p, const UnitTab& ut, hipStre
 // Fused single-kernel path (router + both layers + mix + store); returns
 // hipErrorNotSupported when the sizes have no fused instantiation.
 bool fused_supported(const Problem& p);
+// Split of the last tiles of a dense launch of n_units units (part unset), and
+// the scratch bytes it needs (0: no split)
+FusedSplit fused_split_plan(const Problem& p, int n_units, size_t* bytes);
 hipError_t launch_bf16_fused(const Problem& p, const UnitTab& ut, hipStream_t stream);
 // Routed path: router -> per-token Top-K lists; per-unit counting sort of the
 // (token, translator) assignments into translator-contiguous lists and row

@@ -1,0 +1,116 @@
+"""The fused kernel's split tiles (mot_translate_scratch): the last tiles of a
+launch cut along E*hidden over several workgroups, fp32 partial rows summed by
+a second kernel, against the same call unsplit and the CPU oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2607_28979_amd import binding as mb
+from paper_2607_28979_amd.configs import WORKLOADS, small_variant
+from paper_2607_28979_amd.inputs import generate
+
+from helpers import TOL, dst_shape, max_unit_error, oracle_dims, to_dev
+
+
+def _scratch_bytes(w, lm):
+    lm = np.ascontiguousarray(lm, dtype=np.int32)
+    c = mb.Shapes.from_workload(w).c()
+    return mb.load_library().mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+
+
+def test_scratch_rule():
+    """Bytes are whole fp32 tiles; no split when the tiles fill the chip, on the
+    other paths, or for invalid arguments."""
+    head = WORKLOADS[3]
+    one = _scratch_bytes(head.with_(B=1, T=37), range(28))
+    assert one > 0 and one % (56 * 128 * 512 * 4) == 0
+    assert _scratch_bytes(head, range(28)) == 0                          # 56 full rounds
+    assert _scratch_bytes(head.with_(B=1, T=37, top_k=1), range(28)) == 0
+    assert _scratch_bytes(WORKLOADS[2].with_(B=1, T=37), range(28)) == 0   # two-GEMM shape
+    assert _scratch_bytes(head.with_(T=-1), range(28)) == 0
+    assert _scratch_bytes(head.with_(B=1, T=37), [-1] * 28) == 0
+    lib, c = mb.load_library(), mb.Shapes.from_workload(head.with_(B=1, T=37)).c()
+    assert lib.mot_translate_scratch_bytes(ctypes.byref(c), None) == 0
+
+
+# (workload, variant): one token, a partial tile of each row count (128 and 96),
+# several parts that do not divide the walk, full tiles ahead of the split ones
+# (one workgroup per CU, and two), usage, an unmapped layer, BHTD
+CASES = {
+    "one-token": (3, dict(L_src=2, L_tgt=2, B=1, T=1), {}),
+    "odd-parts": (3, dict(L_src=1, L_tgt=3, B=3, T=45, hidden=192), dict(E=3)),
+    "bhtd": (3, dict(L_src=2, L_tgt=2, B=2, T=37), dict(dst_layout=1, src_layout=1)),
+    "tile-of-96": (4, dict(L_src=2, L_tgt=2, B=1, T=97), {}),
+    "full-and-tail": (4, dict(L_src=1, L_tgt=3, B=1, T=6337, hidden=256), dict(E=4)),
+    "two-per-cu": (1, dict(L_src=1, L_tgt=2, B=1, T=16777), {}),
+    "masked-top2": (3, dict(L_src=2, L_tgt=3, B=1, T=65), dict(top_k=2)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_matches_unsplit(name, oracle_built):
+    import torch
+    from oracle import oracle_translate
+    base, var, kw = CASES[name]
+    w = small_variant(WORKLOADS[base], **var).with_(**kw)
+    lm = np.arange(w.L_tgt, dtype=np.int32) % w.L_src
+    if w.L_tgt == 3:
+        lm[1] = -1
+    inp = generate(w)
+    d = {n: to_dev(getattr(inp, n), w.dtype) for n in ("src_k", "src_v", "w1", "b1", "w2", "b2", "wr", "br")}
+    sh = mb.Shapes.from_workload(w, algo=mb.ALGO_FUSED)
+    c = sh.c()
+    lib = mb.load_library()
+    n = lib.mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+    print("case", name, "scratch", n, flush=True)
+    assert n > 0
+    got = {}
+    for mode in ("split", "whole"):
+        out = [torch.full(dst_shape(w), -3.75, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        use = torch.zeros((w.L_tgt, 2, w.E), dtype=torch.int32, device="cuda")
+        args = (d["src_k"], d["src_v"], lm, d["w1"], d["b1"], d["w2"], d["b2"], d["wr"], d["br"], *out, sh)
+        (mb.translate if mode == "split" else mb.translate_raw)(*args, usage=use)
+        torch.cuda.synchronize()
+        got[mode] = [x.float().cpu().numpy().astype(np.float64) for x in out] + [use.cpu().numpy()]
+    assert np.array_equal(got["split"][2], got["whole"][2])
+    for a, b in zip(got["split"][:2], got["whole"][:2]):
+        # the same bf16 value, or its neighbour where the two fp32 sums fall on
+        # either side of a rounding boundary (sums of hundreds of terms: 1e-5 of
+        # the row's rms covers them where terms cancel)
+        assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(b) + 1e-5 * np.sqrt(np.mean(b * b)))
+        assert np.mean(a != b) < 0.01
+    if w.n_tok <= 256:
+        ref = oracle_translate(oracle_dims(w), inp.src_k, inp.src_v, lm, inp.w1, inp.b1, inp.w2, inp.b2, inp.wr,
+                               inp.br)
+        assert max_unit_error(*got["split"][:2], *ref, w, lm) <= TOL["bf16"]
+
+
+@pytest.mark.gpu
+def test_split_under_graph_capture():
+    """The scratch of a captured call belongs to the graph: replays between
+    eager calls give the eager result."""
+    import torch
+    w = small_variant(WORKLOADS[3], L_src=2, L_tgt=2, B=1, T=37)
+    inp = generate(w)
+    d = {n: to_dev(getattr(inp, n), w.dtype) for n in ("src_k", "src_v", "w1", "b1", "w2", "b2", "wr", "br")}
+    out = [[torch.zeros(dst_shape(w), dtype=torch.bfloat16, device="cuda") for _ in range(2)] for _ in range(2)]
+    sh = mb.Shapes.from_workload(w)
+
+    def call(o):
+        mb.translate(d["src_k"], d["src_v"], [0, 1], d["w1"], d["b1"], d["w2"], d["b2"], d["wr"], d["br"], *o, sh)
+
+    call(out[0])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out[1])
+    for _ in range(3):
+        for o in out[1]:
+            o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(*out))
+        call(out[0])
+        torch.cuda.synchronize()
