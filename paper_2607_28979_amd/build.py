@@ -21,7 +21,7 @@ LIB = os.path.join(CSRC, "libmot.so")
 # (source, object name, preprocessor definitions); the fused kernel's
 # instantiation file is compiled once per (d_in, d_out) so they build in parallel
 SOURCES = [(f, os.path.splitext(f)[0], {}) for f in
-           ("mot_api.hip", "k_router.hip", "k_routed.hip", "k_f32.hip", "k_f32_mfma.hip", "k_bf16_unfused.hip", "k_bf16_gemm256.hip",
+           ("mot_api.hip", "k_router.hip", "k_routed.hip", "k_f32.hip", "k_f32_split.hip", "k_bf16_unfused.hip", "k_bf16_gemm256.hip",
             "k_bf16_fused.hip", "k_project.hip", "k_replay.hip", "k_backbone.hip")]
 SOURCES += [("k_bf16_fused_inst.hip", "k_bf16_fused_%d_%d" % (a, b),
              {"MOT_FUSED_D_IN": a, "MOT_FUSED_D_OUT": b})
@@ -30,7 +30,8 @@ SOURCES += [("k_bf16_fused_inst.hip", "k_bf16_fused_%d_%d" % (a, b),
 # accumulators in VGPRs (the attention softmax rescales them in place and the
 # GEMM epilogues read them; the AGPR form copies them in and out)
 _VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-EXTRA = {f: _VGPR_FORM for f in ("k_replay.hip", "k_backbone.hip", "k_project.hip", "k_bf16_unfused.hip")}
+EXTRA = {f: _VGPR_FORM for f in ("k_replay.hip", "k_backbone.hip", "k_project.hip", "k_bf16_unfused.hip",
+                            "k_f32_split.hip")}
 
 
 def hipcc() -> str:

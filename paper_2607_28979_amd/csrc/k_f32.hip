@@ -1,4 +1,4 @@
-// fp32 translation path for shapes the matrix-core form (k_f32_mfma.hip)
+// fp32 translation path for shapes the matrix-core form (k_f32_split.hip)
 // does not take (hidden not a multiple of 64): two LDS-tiled GEMMs on the
 // vector ALUs.  Built without packed fp32 instructions, the vector ALUs peak
 // at half of MI355X's 157.3 TFLOP/s fp32 figure (one FMA per lane and cycle).

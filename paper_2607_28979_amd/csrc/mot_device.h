@@ -114,9 +114,25 @@ __device__ __forceinline__ void topk_list(const float (&g)[EMAX], int E, int K, 
     }
 }
 
-// Exact-erf GELU, x * Phi(x), with the device erff.
+// Erf GELU, x * Phi(x), for the fp32 paths: 2 Phi(-t) = 2^p(t) for t = |x|, p a
+// degree-8 polynomial through 0 fitted to log2(2 Phi(-t)) (iteratively
+// reweighted least squares, weighted for the absolute error of Phi: 8e-9).
+// Branch-free, 13 vector operations and one exp2, a fifth of the device erff's;
+// in fp32 it is within 4.0e-7 of x Phi(x) on [-9, 9] and rms 3.5e-8 of the rms
+// value over normal x (0.5 x (1 + erff(x / sqrt 2)): 4.5e-7 and 3.7e-8).  p
+// falls monotonically, so large negative x give -0; NaN and infinities as the
+// product with x gives them.
 __device__ __forceinline__ float gelu_erf(float x) {
-    return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
+    const float t = fabsf(x);
+    float p = fmaf(t, -2.8347538e-06f, 3.9376089e-05f);
+    p = fmaf(t, p, -1.8617391e-04f);
+    p = fmaf(t, p, -1.3694886e-04f);
+    p = fmaf(t, p, 7.0634331e-03f);
+    p = fmaf(t, p, -5.2496184e-02f);
+    p = fmaf(t, p, -4.5920819e-01f);
+    p = fmaf(t, p, -1.1511052f);
+    const float h = 0.5f * __builtin_amdgcn_exp2f(t * p);
+    return x * (x < 0.f ? h : 1.0f - h);
 }
 
 // g * GELU(x) with hg = g / 2, for the fused bf16 kernel, in the tanh form
