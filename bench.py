@@ -416,23 +416,17 @@ def cpu_baseline_moth(w, inp, lm, proj, rows):
             "seconds": round(dt, 2)}
 
 
-def pair_gathered_rows(idx, T: int) -> float:
-    """Key rows the two-position sparse kernel gathers per KV head for one
-    launch: for each pair (u, u+1) of every batch row, the size of the union
-    of their (ascending) sets when it is at most 192, else both sets."""
+def group_gathered_rows(idx, T: int) -> float:
+    """Key rows the four-position sparse kernel gathers per KV head for one
+    launch: for each group of positions u .. u+3 of every batch row, the size of
+    the union of their (ascending) sets."""
     import torch
     B, _, S = idx.shape
-    tp = T // 2 * 2
-    a = idx[:, 0:tp:2].long()
-    b = idx[:, 1:tp:2].long()
-    na = (a >= 0).sum(-1)
-    nb = (b >= 0).sum(-1)
-    common = ((a.unsqueeze(-1) == b.unsqueeze(-2)) & (a.unsqueeze(-1) >= 0)).sum((-1, -2))
-    union = na + nb - common
-    rows = torch.where(union <= 192, union, na + nb).sum().item()
-    if T % 2:
-        rows += (idx[:, T - 1] >= 0).sum().item()
-    return float(rows)
+    pad = idx.new_full((B, -T % 4, S), -1)
+    sets = torch.cat([idx, pad], 1).view(B, -1, 4 * S).sort(-1).values
+    new = sets >= 0
+    new[..., 1:] &= sets[..., 1:] != sets[..., :-1]
+    return float(new.sum().item())
 
 
 def bench_replay(args):
@@ -514,15 +508,14 @@ def bench_replay(args):
     # selected K and V rows it gathers per (query, KV head) are reported beside
     sp_gather_sets = 2.0 * 2 * w.D * w.H_kv * w.B * sum(min(u + 1, w.S) for u in range(w.T))
     sp_gather = sp_gather_sets
-    pair = w.D in (64, 128) and w.S <= 128 and 2 * (w.H_q // w.H_kv) <= 16   # the library's rule for that kernel
-    if pair:
-        # the two-position kernel gathers the union of a pair's sets once (or
-        # both sets when the union exceeds its 192-key limit): count the rows
-        # on this run's own sets, averaged over the sparse layers
+    group = 4 * (w.H_q // w.H_kv) <= 32   # the library's rule for that kernel
+    if group:
+        # the four-position kernel gathers the union of a group's sets once:
+        # count the rows on this run's own sets, averaged over the sparse layers
         rows_all = 0.0
         for l in range(w.L_full, w.L_tgt):
             mb.topS_select(maps[int(pi[l])], idx, w.B, w.T, w.S)
-            rows_all += pair_gathered_rows(idx, w.T)
+            rows_all += group_gathered_rows(idx, w.T)
         sp_gather = 2.0 * 2 * w.D * w.H_kv * rows_all / (w.L_tgt - w.L_full)
     sp_bytes = 2.0 * 2 * n_tok * w.H_q * w.D + 4.0 * n_tok * w.S + 2.0 * 2 * n_tok * w.H_kv * w.D
     peak_bf16 = PEAK_TFLOPS["bf16"]
@@ -545,7 +538,7 @@ def bench_replay(args):
     share = {"select": avg["select"] * (w.L_tgt - w.L_full), "sparse": avg["sparse"] * (w.L_tgt - w.L_full),
              "causal": avg["causal"] * w.L_full}
     dom = max(share, key=share.get)
-    kname = {"select": "k_topS_select", "sparse": "k_sparse_attn_pair" if pair else "k_sparse_attn",
+    kname = {"select": "k_topS_select", "sparse": "k_sparse_attn_group" if group else "k_sparse_attn",
              "causal": "k_causal_attn"}
     roof = dict(rows[dom], kernel=kname[dom],
                 traffic=measured_traffic("k_replay.hip", "k_replay", "qwen2.5-7b-replay-8k") if dom == "sparse" else None)

@@ -4,14 +4,17 @@
 // * k_topS_select: for each query position u, the S key positions v <= u
 //   with the largest head-averaged source attention A[b][u][v] (ties to the
 //   lower position), in ascending position order, padded with -1.  Radix
-//   select over order-preserving 32-bit keys: a 1024-bin histogram of the
-//   top 10 bits finds the bin holding the S-th largest key; that bin's keys
+//   select over order-preserving 32-bit keys: a lower bound from the threads'
+//   largest keys, then a 1024-bin histogram of the top 10 bits above it finds the bin holding the S-th largest key; that bin's keys
 //   (a few dozen on attention rows) are ranked against each other for the
 //   exact key, or, past 256 of them, 8-bit radix passes over the lower bits
 //   finish the search; then one ordered pass keeps every larger key and the
 //   lowest-positioned equal ones.
-// * k_sparse_attn: attention of every query head of (b, u) over its key set
-//   (grouped-query: query head h reads KV head h / G).  Per KV head the
+// * k_sparse_attn_group: attention of every query head over the key sets
+//   (grouped-query: query head h reads KV head h / G), four positions and one
+//   KV head per wave over the union of the positions' sets, for G <= 8.
+// * k_sparse_attn: the same for one position (more than 8 query heads per KV
+//   head, or K of 2 GiB and more per batch row).  Per KV head the
 //   workgroup computes scores^T = K_sel . Q^T on v_mfma_f32_16x16x32_bf16 with
 //   the gathered key rows loaded straight into A operands, a softmax over the
 //   set, and O^T = V_sel^T . P^T with V_sel staged transposed in LDS.
@@ -54,12 +57,103 @@ constexpr int kSelBits = 10, kSelBins = 1 << kSelBits;   // first radix digit
 constexpr int kSelCand = 256;                              // boundary-bin keys ranked directly
 static_assert(kSelBins == 4 * 256, "four first-digit bins per thread");
 
-// grid (T, B), 256 threads; CACHE: the row's keys live in dynamic LDS (T words)
-// ahead of the per-chunk counts
-template <bool CACHE>
-__global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* idx, int T, int S) {
-    extern __shared__ uint32_t s_key[];
+// Where a selection's keys come from.  RegKeys: the row in registers, NV 16-byte
+// pieces per thread (piece i of thread t: positions 1024 i + 4 t .. +3), for T <=
+// 1024 NV.  RowKeys: read from the row again in every pass, one per thread and
+// 256 positions (longer rows).
+//
+// for_each<EXACT>(f): f(key) for every position < n of this thread, and, unless
+// EXACT, f(0) for others (0 is the least key); chunks(f): f(chunk,
+// this lane's Q keys, their first position, n) for each chunk of 64 Q positions of
+// this wave, by all its lanes (positions >= n among them).
+template <int NV>
+struct RegKeys {
+    static constexpr int Q = 4;
+    // waves per SIMD the registers are limited to (NV = 8: 6 measured best of 4, 6, 8)
+    static constexpr int WAVES = NV <= 8 ? 6 : 4;
+    u32x4 k[NV];
+    int n;
+    __device__ __forceinline__ void load(const float* row, int T, int n_) {
+        n = n_;
+        const bool whole = (T & 3) == 0;   // rows are 16-byte aligned (T % 4 == 0): a
+        // piece may end past u, still inside the row; the rest is never used
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int v = 1024 * i + 4 * threadIdx.x;
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+            if (v < n) {
+                if (whole) {
+                    a = *reinterpret_cast<const f32x4*>(row + v);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (v + c < n) a[c] = row[v + c];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) k[i][c] = v + c < n ? order_key(a[c]) : 0u;
+        }
+    }
+    // n as a new value in each pass: the comparisons with it are made again
+    // instead of being kept in scalar registers (which spills them)
+    __device__ __forceinline__ int bound() const {
+        int m = n;
+        asm volatile("" : "+s"(m));
+        return m;
+    }
+    template <bool EXACT, class F>
+    __device__ __forceinline__ void for_each(F f) const {
+        const int m = bound();
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            if (1024 * i < m)   // uniform
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (!EXACT || 1024 * i + 4 * (int)threadIdx.x + c < m) f(k[i][c]);
+    }
+    template <class F>
+    __device__ __forceinline__ void chunks(F f) const {
+        const int m = bound();
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            if (1024 * i < m) f(4 * i + (threadIdx.x >> 6), k[i], 1024 * i + 4 * (int)threadIdx.x, m);
+    }
+};
+
+struct RowKeys {
+    static constexpr int Q = 1, WAVES = 8;
+    const float* row;
+    int n;
+    __device__ __forceinline__ void load(const float* r, int, int n_) {
+        row = r;
+        n = n_;
+    }
+    template <bool EXACT, class F>
+    __device__ __forceinline__ void for_each(F f) const {
+        for (int v = threadIdx.x; v < n; v += 256) f(order_key(row[v]));
+    }
+    template <class F>
+    __device__ __forceinline__ void chunks(F f) const {
+        for (int v0 = 0; v0 < n; v0 += 256) {
+            const int v = v0 + threadIdx.x;
+            const uint32_t k[1] = {v < n ? order_key(row[v]) : 0u};
+            f(v >> 6, k, v, n);
+        }
+    }
+};
+
+// Bound: vector instructions per key.  8192 rows of a causal map, sets of 128: 120
+// us with the row's keys in LDS (4 workgroups per CU, every key counted by an LDS
+// atomic), 60 us with them in registers and one key in ten counted.
+//
+// grid (T, B), 256 threads; dynamic LDS: per-chunk counts s_gt, s_eq
+// (T / (64 Q) + 4 each)
+template <class Keys>
+__global__ __launch_bounds__(256, Keys::WAVES) void k_topS_select(const float* A, int32_t* idx, int T, int S) {
+    extern __shared__ int s_gt[];
+    constexpr int Q = Keys::Q;
     __shared__ uint32_t hist[kSelBins];
+    __shared__ uint32_t hist_max[kSelBins];
     __shared__ uint32_t s_cand[kSelCand];
     __shared__ uint32_t s_sel[3], s_wsum[4];
     __shared__ int s_cnt;
@@ -70,51 +164,25 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
         for (int c = tid; c < S; c += 256) out[c] = c < n ? c : -1;
         return;
     }
-    const float* row = A + ((size_t)b * T + u) * T;
-    // dynamic LDS: [CACHE: T keys] then per-chunk counts s_gt, s_eq (T/64 + 1 each)
-    int* s_gt = reinterpret_cast<int*>(s_key + (CACHE ? T : 0));
-    int* s_eq = s_gt + (T >> 6) + 1;
-    if constexpr (CACHE) {
-        // fill the key cache with 16-byte loads, several in flight per thread
-        // (rows are 16-byte aligned when T % 4 == 0; the last piece may read
-        // positions past u, still inside the row, and they are never used)
-        if ((T & 3) == 0) {
-            const f32x4* row4 = reinterpret_cast<const f32x4*>(row);
-            u32x4* key4 = reinterpret_cast<u32x4*>(s_key);
-            const int n4 = (n + 3) >> 2;
-#pragma unroll 4
-            for (int v = tid; v < n4; v += 256) {
-                const f32x4 a = row4[v];
-                key4[v] = u32x4{order_key(a.x), order_key(a.y), order_key(a.z), order_key(a.w)};
-            }
-        } else {
-#pragma unroll 8
-            for (int v = tid; v < n; v += 256) s_key[v] = order_key(row[v]);
-        }
-        __syncthreads();
-    }
-    // first digit: the top kSelBits bits (sign, exponent and one mantissa bit)
-    constexpr int sh1 = 32 - kSelBits;
-    auto key_at = [&](int v) -> uint32_t {
-        if constexpr (CACHE) return s_key[v];
-        else return order_key(row[v]);
-    };
+    int* s_eq = s_gt + T / (64 * Q) + 4;
+    Keys keys;
+    keys.load(A + ((size_t)b * T + u) * T, T, n);
+    // first digit: the top kSelBits bits (sign, exponent and one mantissa bit).
     // 1024 bins: an attention row's keys crowd into a few exponents, and with
     // an 8-bit first digit the boundary bin held ~70 keys and needed another
     // full radix pass; with 10 bits it holds a few dozen, ranked directly.
+    constexpr int sh1 = 32 - kSelBits;
     if (tid < 64) s_cnt = 0;
 #pragma unroll
-    for (int i = 0; i < kSelBins / 256; ++i) hist[tid + 256 * i] = 0;
+    for (int i = 0; i < kSelBins / 256; ++i) hist[tid + 256 * i] = hist_max[tid + 256 * i] = 0;
     __syncthreads();
-    for (int v = tid; v < n; v += 256) atomicAdd(&hist[key_at(v) >> sh1], 1u);
-    __syncthreads();
-    {
-        // thread t holds bins 4t .. 4t+3: suffix sums over the threads (within
-        // each wave by shuffles, then the higher waves' totals) find the bin
-        // holding the S-th largest key
+    // the bin of h holding the S-th largest key -> s_sel: thread t holds bins
+    // 4t .. 4t+3, suffix sums over the threads (within each wave by shuffles, then
+    // the higher waves' totals); ends in a barrier
+    auto find_bin = [&](const uint32_t* h) {
         const int lane = tid & 63, wv = tid >> 6;
-        const uint32_t h0 = hist[4 * tid], h1 = hist[4 * tid + 1], h2 = hist[4 * tid + 2], h3 = hist[4 * tid + 3];
-        const uint32_t c = h0 + h1 + h2 + h3;
+        const uint32_t hb[4] = {h[4 * tid], h[4 * tid + 1], h[4 * tid + 2], h[4 * tid + 3]};
+        const uint32_t c = hb[0] + hb[1] + hb[2] + hb[3];
         uint32_t suf = c;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -126,9 +194,8 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
         for (int q = wv + 1; q < 4; ++q) suf += s_wsum[q];
         if (suf >= (uint32_t)S && suf - c < (uint32_t)S) {
             uint32_t cum = suf - c;   // keys in bins above 4t+3
-            const uint32_t hb[4] = {h0, h1, h2, h3};
             int d = 4 * tid;
-            uint32_t cnt = h0;
+            uint32_t cnt = hb[0];
 #pragma unroll
             for (int q = 3; q >= 0; --q) {
                 if (cum + hb[q] >= (uint32_t)S) {
@@ -142,20 +209,40 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
             s_sel[1] = cum;
             s_sel[2] = cnt;
         }
+        __syncthreads();
+    };
+    // A lower bound first: when every thread holds a key and S <= 256, S of the
+    // threads' largest keys reach the bin of the S-th largest of those, so the
+    // row's S-th largest key does too, and the keys below that bin (nine in ten
+    // of a long row) need no atomic
+    uint32_t d0 = 0;
+    if (S <= 256 && n >= 256 * Q) {   // uniform
+        uint32_t mx = 0;
+        keys.template for_each<false>([&](uint32_t k) { mx = k > mx ? k : mx; });
+        atomicAdd(&hist_max[mx >> sh1], 1u);
+        __syncthreads();
+        find_bin(hist_max);
+        d0 = s_sel[0];
     }
+    const auto count = [&](uint32_t k) {
+        if ((k >> sh1) >= d0) atomicAdd(&hist[k >> sh1], 1u);
+    };
+    if (d0 > 0) keys.template for_each<false>(count);   // uniform
+    else keys.template for_each<true>(count);
     __syncthreads();
+    find_bin(hist);
     const uint32_t d1 = s_sel[0], cnt1 = s_sel[2];
     int rem = S - (int)s_sel[1];   // keys still to choose in the boundary bin
     uint32_t prefix = d1 << sh1, mask = ~0u << sh1;
+    bool all_eq = cnt1 == (uint32_t)rem;   // every key equal to prefix under mask is taken (uniform)
     if (cnt1 != (uint32_t)rem) {   // uniform: not every key of the boundary bin is taken
         if (cnt1 <= (uint32_t)kSelCand) {
             // the boundary bin's keys, ranked against each other: the rem-th
             // largest is the S-th largest of the row, and the keys equal to it
             // that are taken are the first ones in position order
-            for (int v = tid; v < n; v += 256) {
-                const uint32_t k = key_at(v);
+            keys.template for_each<true>([&](uint32_t k) {
                 if ((k >> sh1) == d1) s_cand[atomicAdd(&s_cnt, 1)] = k;
-            }
+            });
             __syncthreads();
             if (tid < (int)cnt1) {
                 const uint32_t ki = s_cand[tid];
@@ -168,12 +255,14 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
                 if (gt < rem && rem <= gt + eq) {   // every such thread writes the same pair
                     s_sel[0] = ki;
                     s_sel[1] = (uint32_t)(rem - gt);
+                    s_sel[2] = gt + eq == rem;
                 }
             }
             __syncthreads();
             prefix = s_sel[0];
             mask = ~0u;
             rem = (int)s_sel[1];
+            all_eq = s_sel[2];
         } else {
             // many keys share the digit: 8-bit radix passes over the bits
             // below it (a last digit that overlaps resolved bits is harmless:
@@ -183,10 +272,9 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
                 const int shift = sh;
                 hist[tid] = 0;
                 __syncthreads();
-                for (int v = tid; v < n; v += 256) {
-                    const uint32_t k = key_at(v);
+                keys.template for_each<true>([&](uint32_t k) {
                     if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
-                }
+                });
                 __syncthreads();
                 if (tid < 64) {
                     // lane l holds bins 4l .. 4l+3; suffix sums over lanes find the
@@ -228,26 +316,80 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
                 mask |= 255u << shift;
                 __syncthreads();
                 // every key of the boundary bin is taken: the digits below decide nothing
-                if (cnt == (uint32_t)rem) break;
+                all_eq = cnt == (uint32_t)rem;
+                if (all_eq) break;
             }
         }
     }
     // prefix is the S-th largest key on the resolved digits (k & mask): take
     // every key larger under the mask and the first rem equal ones in
     // position order (all of them after an early stop).  Rows are cut into
-    // 64-position chunks (chunk c: positions 64c + lane, wave c % 4):
-    // per-chunk counts of larger and equal keys, one scan over the chunks,
-    // then each chunk writes its picks at its offset in ballot order.
-    const int lane = tid & 63, wv = tid >> 6, nch = (n + 63) >> 6;
-    for (int c = wv; c < nch; c += 4) {
-        const int v = 64 * c + lane;
-        const uint32_t k = v < n ? key_at(v) & mask : 0u;
-        const unsigned long long bg = __ballot(v < n && k > prefix), be = __ballot(v < n && k == prefix);
-        if (lane == 0) {
-            s_gt[c] = __popcll(bg);
-            s_eq[c] = __popcll(be);
+    // chunks of 64 Q positions, Q consecutive ones per lane of one wave: per-chunk
+    // counts of larger and equal keys, one scan over the chunks, then each chunk
+    // writes its picks at its offset, lane by lane.
+    const int lane = tid & 63, nch = (n + 64 * Q - 1) / (64 * Q);
+    // set bits of b in the lanes below this one, plus add
+    const auto below = [](unsigned long long b, int add) {
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, add));
+    };
+    if (all_eq && prefix > 0) {   // uniform; nearly every row: no ranks among the equal keys
+        // (keys of positions >= n are 0 and fall out by themselves)
+        keys.chunks([&](int c, const auto& k, int, int) {
+            int take = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) take += __popcll(__ballot((k[q] & mask) >= prefix));
+            if (lane == 0 && c < nch) s_gt[c] = take;
+        });
+        __syncthreads();
+        if (tid < 64) {   // exclusive scan: lane l owns chunks [l*cpl, l*cpl + cpl)
+            const int cpl = (nch + 63) >> 6, c0 = tid * cpl, c1 = min(c0 + cpl, nch);
+            int own = 0;
+            for (int c = c0; c < c1; ++c) own += s_gt[c];
+            int pre = own;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int t = __shfl_up(pre, off, 64);
+                if (tid >= off) pre += t;
+            }
+            pre -= own;
+            for (int c = c0; c < c1; ++c) {
+                const int t = s_gt[c];
+                s_gt[c] = pre;
+                pre += t;
+            }
         }
+        __syncthreads();
+        keys.chunks([&](int c, const auto& k, int v, int) {
+            if (c >= nch) return;   // uniform over the wave
+            int pos = s_gt[c];
+            bool take[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                take[q] = (k[q] & mask) >= prefix;
+                pos = below(__ballot(take[q]), pos);
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (take[q]) {
+                    if (pos < S) out[pos] = v + q;
+                    ++pos;
+                }
+        });
+        return;
     }
+    keys.chunks([&](int c, const auto& k, int v, int n) {
+        int gt = 0, eq = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint32_t kq = k[q] & mask;
+            gt += __popcll(__ballot(v + q < n && kq > prefix));
+            eq += __popcll(__ballot(v + q < n && kq == prefix));
+        }
+        if (lane == 0 && c < nch) {
+            s_gt[c] = gt;
+            s_eq[c] = eq;
+        }
+    });
     __syncthreads();
     if (tid < 64) {
         // exclusive scans over chunks: lane l owns chunks [l*cpl, l*cpl + cpl)
@@ -285,17 +427,31 @@ __global__ __launch_bounds__(256) void k_topS_select(const float* A, int32_t* id
         }
     }
     __syncthreads();
-    for (int c = wv; c < nch; c += 4) {
-        const int v = 64 * c + lane;
-        const uint32_t k = v < n ? key_at(v) & mask : 0u;
-        const bool eq = v < n && k == prefix;
-        const unsigned long long be = __ballot(eq);
-        const int eq_rank = s_eq[c] + __popcll(be & ((1ull << lane) - 1ull));
-        const bool take = (v < n && k > prefix) || (eq && eq_rank < rem);
-        const unsigned long long bt = __ballot(take);
-        const int pos = s_gt[c] + __popcll(bt & ((1ull << lane) - 1ull));
-        if (take && pos < S) out[pos] = v;
-    }
+    keys.chunks([&](int c, const auto& k, int v, int n) {
+        if (c >= nch) return;   // uniform over the wave
+        int eq_rank = s_eq[c], pos = s_gt[c];   // before this lane's keys
+        bool gt[Q], eq[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint32_t kq = k[q] & mask;
+            gt[q] = v + q < n && kq > prefix;
+            eq[q] = v + q < n && kq == prefix;
+            eq_rank = below(__ballot(eq[q]), eq_rank);
+        }
+        bool take[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            take[q] = gt[q] || (eq[q] && eq_rank < rem);
+            eq_rank += eq[q];
+            pos = below(__ballot(take[q]), pos);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (take[q]) {
+                if (pos < S) out[pos] = v + q;
+                ++pos;
+            }
+    });
 }
 
 __device__ __forceinline__ size_t kv_row(const ReplayProblem& p, int b, int t, int kvh) {
@@ -312,6 +468,22 @@ __device__ __forceinline__ int xcd_item(int id, int n) { return (id & 7) * ((n +
 inline int xcd_grid(int n) { return 8 * ((n + 7) / 8); }
 
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// LDS swizzle of a row of D bf16 (K rows: chunk c at c ^ causal_kswz(row))
+template <int D>
+__device__ __forceinline__ int causal_kswz(int r) {   // K rows: D/8 chunks
+    return D == 128 ? (r & 15) : ((r >> 1) & 7);
+}
+
+// four bf16 of 16-byte chunk `at` (half 0 or 1) per lane, transposed within 16
+// lanes: lane i's 8 bytes are row i / 4, columns 4 (i % 4) .. +3 of a 4 x 16
+// block, and it gets column i of the four rows
+__device__ __forceinline__ u32x2 read_tr16(const u32x4* at, int half) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const u32x2* q = reinterpret_cast<const u32x2*>(at) + half;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)q));
+}
 
 // 8 bf16 of chunk a (keys k0) and c (key k0+1) interleaved into 8 words:
 // word i = (a[i], c[i]) for d = 8*chunk + i
@@ -475,246 +647,334 @@ __global__ __launch_bounds__(256) void k_sparse_attn(ReplayProblem p) {
     }
 }
 
-// Two neighbouring positions per workgroup (grouped-query heads G <= 8, sets
-// of up to 128 keys): u0 = 2 * item and u0 + 1 attend over the union of
-// their two sets, each key gathered once, with a per-position membership
-// mask.  The 2G query heads of the pair are the B columns of the score
-// product (16 columns), so the two positions share every gathered K and V row
-// and every MFMA.  Column c < 2G is position pp = c / G, head c % G.
+// Four neighbouring positions per group (grouped-query heads G <= 8): u0 .. u0+3
+// attend over the union of their key sets, each key gathered once, with a mask
+// of the positions that list it.  Neighbouring positions attend to nearly the
+// same keys (sets of 128 over a map of locality, sinks and heavy hitters: four
+// positions' union is ~155 keys), and the 4G query heads are the columns of
+// 32x32 products.
 //
-// The union: when both sets are ascending with their -1 padding at the end
-// (what the Top-S selection writes), it is set 0 followed by the keys of set 1
-// that set 0 lacks (binary search), and a key of set 0 belongs to position 1
-// if set 1 holds it.  When the union exceeds kPairKeys keys, or a set is not
-// ascending (unordered, duplicates), the workgroup makes two passes instead,
-// one per position over that position's set as listed, and stores only that
-// position's columns.  A position attends to the entries of its bit that lie
-// in 0 .. u0 + pp.
+// A wave runs one (group, KV head) by itself, with no barrier: WPG waves share
+// a group's key list (KV heads w, w + WPG, ...), 4 / WPG groups per workgroup.
+// It walks the list in blocks of 32 keys with an online softmax, as the causal
+// kernel does: K and V rows come straight into LDS (buffer loads, a whole row by
+// 16 or 8 lanes; entries past the list read as zeros), the next block's K while
+// this block's softmax and P . V run, its V while the next scores do.
+// scores^T[key][column] takes K rows as A operands; in O^T[d][column] += V^T .
+// P^T a lane's accumulators hold keys 8i + 4g + {0..3}, which is the order in
+// which two transposing LDS reads (four keys of one d each) give the V^T
+// operand, so neither P nor V is rearranged.
 //
-// grid (xcd_grid(ceil(T / 2)), B), 256 threads
-constexpr int kPairKeys = 192;   // largest union one pass takes (register arrays and LDS are sized for it)
+// The list: with ascending sets (-1 padding last, what the Top-S selection
+// writes) the entries of set p that no earlier set holds, in set order, with the
+// mask of all sets that hold them (binary searches).  If a set of the group is
+// not ascending (unordered, duplicates), every entry as listed, for its own
+// position.  Entries outside 0 .. u of their position are left out.
+//
+// Bound: latency (waves wait half their time; 2 per SIMD is what the tiles and
+// accumulators leave room for).  28 query heads on 4 KV heads of 128, 8192
+// positions, sets of 128: 252 us with two positions per workgroup and V transposed
+// by 4-byte LDS stores, 88 us now (0.67 GB gathered instead of 1.2).
+//
+// grid xcd_grid(ceil(B * ceil(T / 4) / (4 / WPG))), 256 threads
+constexpr int kPos = 4;   // positions per group
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void k_sparse_attn_pair(ReplayProblem p) {
-    constexpr int SMAX = 128, UMAX = kPairKeys, DC = D / 8;
-    __shared__ u32x4 s_lds[(D * UMAX + 16 * UMAX) / 8];
-    __shared__ float red[128];
-    __shared__ int s_set[2][SMAX];
-    __shared__ int s_keys[UMAX];
-    __shared__ int s_mask[UMAX];
-    __shared__ int s_cnt[2];
-    const int npair = (p.T + 1) / 2;
-    const int item = xcd_item(blockIdx.x, npair), b = blockIdx.y;
-    if (item >= npair) return;   // uniform over the workgroup
-    const int u0 = 2 * item;
-    const bool has1 = u0 + 1 < p.T;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, q4 = lane >> 4;
+template <int D, int WPG>
+__global__ __launch_bounds__(256, 2) void k_sparse_attn_group(ReplayProblem p) {
+    constexpr int GPW = 4 / WPG, SMAX = replay_sparse_smax(D), ENT = kPos * SMAX;   // entries per group
+    constexpr int CH = SMAX / 64, NCH = kPos * CH;   // rounds of 64 entries of a set, of a group
+    constexpr int DC = D / 8, TILE = 32 * DC;    // 16-byte chunks of a row, of 32 rows
+    constexpr int RPL = 64 / DC, NL = 32 / RPL;  // rows per wave load, loads per tile
+    // per wave a K tile and a V tile (the sets, before the walk), then the lists:
+    // row offsets, masks (a byte each), counts per 64 entries; a flag per wave.  One LDS
+    // object: with a second one (__syncthreads_or brings its own) the compiler
+    // waits for every load into LDS before each LDS read of the walk
+    __shared__ u32x4 s_lds[4 * 2 * TILE + GPW * (ENT / 4 + ENT / 16 + ENT / 256) + 1];
+    static_assert(GPW * ENT * 4 <= 4 * 2 * TILE * 16, "the sets fit the tiles' space");
+    int* s_set = reinterpret_cast<int*>(s_lds);
+    uint32_t* s_row = reinterpret_cast<uint32_t*>(s_lds + 4 * 2 * TILE);
+    uint8_t* s_mask = reinterpret_cast<uint8_t*>(s_row + GPW * ENT);
+    int* s_cnt = reinterpret_cast<int*>(s_mask + GPW * ENT);   // [GPW][NCH]
+    int* s_bad = s_cnt + GPW * NCH;                            // [4]
+    const int ngrp = (p.T + kPos - 1) / kPos, nitem = (p.B * ngrp + GPW - 1) / GPW;
+    const int item = xcd_item(blockIdx.x, nitem);
+    if (item >= nitem) return;   // uniform over the workgroup
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
     const int S = p.S, G = p.H_q / p.H_kv;
-    const uint16_t* Q = reinterpret_cast<const uint16_t*>(p.q);
-    const uint16_t* K = reinterpret_cast<const uint16_t*>(p.k);
-    const uint16_t* V = reinterpret_cast<const uint16_t*>(p.v);
-    uint16_t* O = reinterpret_cast<uint16_t*>(p.o);
+
+    // this wave's group, this lane's column (position pp, head hh of the KV
+    // head's), and its query rows of the first KV head, loaded ahead of the list
+    const int gi = w / WPG, q = item * GPW + gi, b = q / ngrp, u0 = q % ngrp * kPos;
+    const int pp = l32 / G, hh = l32 - pp * G;
+    const bool col_ok = pp < kPos && q < p.B * ngrp && u0 + pp < p.T;
+    u32x4 qop[D / 16];
+    auto load_q = [&](int kvh) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        const uint16_t* row = reinterpret_cast<const uint16_t*>(p.q) +
+                              (((size_t)b * p.T + u0 + pp) * p.H_q + kvh * G + hh) * D + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+            qop[ks] = col_ok && kvh < p.H_kv ? *reinterpret_cast<const u32x4*>(row + 16 * ks) : zero;
+    };
+    load_q(w % WPG);
+
+    // ---- the lists: wave w takes the sets of position w of every group, entry
+    // lane + 64 r in round r
+    const uint32_t ts = p.kv_layout == MOT_LAYOUT_BTHD ? (uint32_t)(p.H_kv * D) : (uint32_t)D;
+    int key[GPW][CH], rank[GPW][CH];
+    uint32_t mask[GPW][CH];
+#pragma unroll
+    for (int j = 0; j < GPW; ++j) {
+        const int qj = item * GPW + j, bj = qj / ngrp, u = qj % ngrp * kPos + w;
+        const int32_t* set = p.idx + ((size_t)bj * p.T + u) * S;
+#pragma unroll
+        for (int r = 0; r < CH; ++r) {
+            const int e = lane + 64 * r;
+            key[j][r] = e < S && qj < p.B * ngrp && u < p.T ? set[e] : -1;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < GPW; ++j)
+#pragma unroll
+        for (int r = 0; r < CH; ++r)
+            if (lane + 64 * r < S) s_set[(j * kPos + w) * S + lane + 64 * r] = key[j][r];
+    __syncthreads();
+    bool bad = false;   // a set that is not ascending
+#pragma unroll
+    for (int j = 0; j < GPW; ++j)
+#pragma unroll
+        for (int r = 0; r < CH; ++r) {
+            const int e = lane + 64 * r, v = key[j][r], nx = e + 1 < S ? s_set[(j * kPos + w) * S + e + 1] : -1;
+            bad |= e < S && ((v < 0 && nx >= 0) || (v >= 0 && nx >= 0 && nx <= v) || v < -1);
+        }
+    const bool wave_bad = __any(bad);
+    if (lane == 0) s_bad[w] = wave_bad;
+    __syncthreads();
+    const bool ordered = !(s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3]);
+    const int top = 1 << (31 - __builtin_clz(S));   // largest power of two <= S
+#pragma unroll
+    for (int j = 0; j < GPW; ++j) {
+        const int uj = (item * GPW + j) % ngrp * kPos;
+        const int* sets = s_set + j * kPos * S;
+        // entries of each set below each key, by bisection, side by side (-1
+        // padding compares as the largest)
+        int at[CH][kPos];
+#pragma unroll
+        for (int r = 0; r < CH; ++r)
+#pragma unroll
+            for (int o = 0; o < kPos; ++o) at[r][o] = 0;
+        for (int step = ordered ? top : 0; step; step >>= 1)
+#pragma unroll
+            for (int r = 0; r < CH; ++r)
+                if (64 * r < S)
+#pragma unroll
+                    for (int o = 0; o < kPos; ++o) {
+                        const int i = at[r][o] + step - 1;
+                        const uint32_t v = (uint32_t)sets[o * S + min(i, S - 1)];
+                        at[r][o] += i < S && v < (uint32_t)key[j][r] ? step : 0;
+                    }
+#pragma unroll
+        for (int r = 0; r < CH; ++r) {
+            bool keep = key[j][r] >= 0 && key[j][r] <= uj + w;
+            mask[j][r] = 1u << w;
+            if (ordered && 64 * r < S) {
+#pragma unroll
+                for (int o = 0; o < kPos; ++o) {
+                    const int v = sets[o * S + min(at[r][o], S - 1)];
+                    // position o attends the key when its set holds it and it is not ahead
+                    if (o != w && at[r][o] < S && v == key[j][r] && v <= uj + o) {
+                        mask[j][r] |= 1u << o;
+                        keep &= o > w;
+                    }
+                }
+            }
+            const unsigned long long bal = __ballot(keep);
+            if (lane == 0) s_cnt[j * NCH + w * CH + r] = __popcll(bal);
+            rank[j][r] = keep ? __popcll(bal & ((1ull << lane) - 1ull)) : -1;
+        }
+    }
+    __syncthreads();
+    int U = 0;   // length of this wave's list
+#pragma unroll
+    for (int j = 0; j < GPW; ++j) {
+        int before = 0, all = 0;   // kept entries ahead of this wave's sets, and in all
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int n = s_cnt[j * NCH + c];
+            before += c < w * CH ? n : 0;
+            all += n;
+        }
+#pragma unroll
+        for (int r = 0; r < CH; ++r) {
+            if (rank[j][r] >= 0) {
+                s_row[j * ENT + before + rank[j][r]] = (uint32_t)key[j][r] * ts * 2;
+                s_mask[j * ENT + before + rank[j][r]] = (uint8_t)mask[j][r];
+            }
+            before += s_cnt[j * NCH + w * CH + r];
+        }
+        // pad to whole blocks with rows past the buffers' ends, for no position
+        if (w == 0 && lane < (32 - all % 32) % 32) {
+            s_row[j * ENT + all + lane] = 0x80000000u;
+            s_mask[j * ENT + all + lane] = 0;
+        }
+        if (j == gi) U = all;
+    }
+    const int nblk = (U + 31) / 32;
+    __syncthreads();
+    if (q >= p.B * ngrp) return;   // uniform over the wave; no barrier follows
+
+    const uint32_t* rowoff = s_row + gi * ENT;
+    const uint8_t* bytemask = s_mask + gi * ENT;
+    const uint32_t* masks = reinterpret_cast<const uint32_t*>(s_mask + gi * ENT);
+    u32x4* Kt = s_lds + w * 2 * TILE;   // row r: chunk c at c ^ causal_kswz(r)
+    u32x4* Vt = Kt + TILE;              // row r: chunk c at c ^ vswz(r), which keeps chunk pairs together
+    auto vswz = [](int r) { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); };
+    const uint32_t bytes = ((uint32_t)(p.T - 1) * ts + D) * 2;   // < 2^31 (replay_causal_supported)
     const float sl2 = kLog2e / sqrtf((float)D);
-    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const uint32_t bit = col_ok ? 1u << pp : 0u;
+    const int lrow = lane / DC, lch = lane % DC;   // this lane's row and chunk of a wave load
+    uint16_t* O = reinterpret_cast<uint16_t*>(p.o);
+    // operand read addresses: V^T by transposing reads, 16 lanes reading 4 keys x
+    // 16 d (lane i of the 16: key i / 4, d 4 (i % 4) .. +3, and gets d = i)
+    const int l16 = lane & 15, vrow = 4 * g + (l16 >> 2), vch = 2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1);
 
-    // ---- the two sets, then their union with membership bits
-    if (tid < 2 * S) {
-        const int pp = tid / S, e = tid % S;
-        s_set[pp][e] = pp == 0 || has1 ? p.idx[((size_t)b * p.T + u0 + pp) * S + e] : -1;
-    }
-    __syncthreads();
-    bool bad = false;
-    if (tid < 2 * S) {
-        const int pp = tid / S, e = tid % S, v = s_set[pp][e], nx = e + 1 < S ? s_set[pp][e + 1] : -1;
-        bad = (v < 0 && nx >= 0) || (v >= 0 && nx >= 0 && nx <= v) || v < -1;
-    }
-    const bool ordered = !__syncthreads_or(bad);
-    // nonnegative prefix lengths of the two sets
-    const int n0 = __syncthreads_count(tid < S && s_set[0][tid] >= 0);
-    const int n1 = __syncthreads_count(tid < S && s_set[1][tid] >= 0);
-    // union (one pass) when ordered and small enough; ext = set 1's extra keys
-    bool extra = false;
-    int v1 = -1;
-    if (ordered && tid < S) {
-        auto find = [&](const int* set, int n, int v) {
-            int lo = 0, hi = n;   // first index with set[i] >= v
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (set[mid] < v) lo = mid + 1;
-                else hi = mid;
+    for (int kvh = w % WPG; kvh < p.H_kv; kvh += WPG) {
+        const rsrc_t kbuf = make_rsrc(reinterpret_cast<const uint16_t*>(p.k) + kv_row(p, b, 0, kvh), bytes);
+        const rsrc_t vbuf = make_rsrc(reinterpret_cast<const uint16_t*>(p.v) + kv_row(p, b, 0, kvh), bytes);
+        // positions of this pass: all four, or, when that gave a value that is not
+        // finite (a V row that a neighbour attends multiplies a probability of 0),
+        // one at a time over its own keys, the others' rows read as zeros
+        uint32_t pm;
+        uint32_t off[NL];   // row offsets of the block whose V is loaded next
+        auto rows = [&](int blk) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) off[i] = rowoff[blk * 32 + i * RPL + lrow];
+            if (pm != 15u) {   // uniform
+#pragma unroll
+                for (int i = 0; i < NL; ++i)
+                    if (!(bytemask[blk * 32 + i * RPL + lrow] & pm)) off[i] = 0x80000000u;
             }
-            return lo < n && set[lo] == v;
         };
-        v1 = s_set[1][tid];
-        extra = tid < n1 && !find(s_set[0], n0, v1);
-        if (tid < n0) {
-            const int v0 = s_set[0][tid];
-            s_keys[tid] = v0;
-            s_mask[tid] = 1 | (find(s_set[1], n1, v0) ? 2 : 0);
-        }
-    }
-    const unsigned long long bal = __ballot(extra);
-    if (lane == 0 && w < 2) s_cnt[w] = __popcll(bal);
-    __syncthreads();
-    const int n_union = n0 + s_cnt[0] + s_cnt[1];
-    const bool one_pass = ordered && n_union <= UMAX;
-    if (one_pass && extra) {
-        const int pos = n0 + (w == 1 ? s_cnt[0] : 0) + __popcll(bal & ((1ull << lane) - 1ull));
-        s_keys[pos] = v1;
-        s_mask[pos] = 2;
-    }
-    // B column of this lane: position pp, head hh (kv head kvh*G + hh)
-    const int pp = l16 / G, hh = l16 - pp * G;
-    const bool col_ok = l16 < 2 * G && (pp == 0 || has1);
-    for (int pass = 0; pass < (one_pass ? 1 : (has1 ? 2 : 1)); ++pass) {
-    // keys of this pass: the union, or set `pass` as listed
-    int U;
-    if (one_pass) {
-        U = n_union;
-    } else {
-        __syncthreads();   // the previous pass has finished with s_keys
-        if (tid < S) {
-            s_keys[tid] = s_set[pass][tid];
-            s_mask[tid] = 1 << pass;
-        }
-        U = S;
-    }
-    // the positions whose columns this pass stores
-    const int store_mask = one_pass ? 3 : 1 << pass;
-    const int UP = U < 32 ? 32 : (U + 31) / 32 * 32;   // rounded up to whole 32-key steps
-    for (int e = U + tid; e < UP; e += 256) {
-        s_keys[e] = -1;
-        s_mask[e] = 0;
-    }
-    __syncthreads();
-
-    const int SC = UP / 8, KB = UP / 16;
-    const int swm = replay_swizzle_mask(SC);
-    u32x4* Vt = s_lds;                      // row d: SC chunks, chunk c at (c ^ (d & swm))
-    u32x4* Pl = s_lds + D * SC;             // row = B column
-    // a key is gathered when some position may attend it
-    auto gather_ok = [&](int kv) { return kv >= 0 && kv <= u0 + (has1 ? 1 : 0); };
-    constexpr int MAXR = replay_sparse_v_items(D, UMAX);
-    constexpr int MAXB = replay_sparse_key_blocks(UMAX);
-
-    for (int kvh = 0; kvh < p.H_kv; ++kvh) {
-        u32x4 va[MAXR], vc[MAXR];
+        auto load_k = [&]() {
 #pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
-            const int it = tid + 256 * r;
-            va[r] = zero;
-            vc[r] = zero;
-            if (it < (UP / 2) * DC) {
-                const int pr = it % (UP / 2), dc = it / (UP / 2), k0 = 2 * pr;
-                const int v0 = s_keys[k0], v1 = s_keys[k0 + 1];
-                if (gather_ok(v0)) va[r] = *reinterpret_cast<const u32x4*>(V + kv_row(p, b, v0, kvh) + 8 * dc);
-                if (gather_ok(v1)) vc[r] = *reinterpret_cast<const u32x4*>(V + kv_row(p, b, v1, kvh) + 8 * dc);
+            for (int i = 0; i < NL; ++i)
+                load_lds16(kbuf, off[i] + 16 * (lch ^ causal_kswz<D>(i * RPL + lrow)), Kt + i * 64);
+        };
+        auto load_v = [&]() {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load_lds16(vbuf, off[i] + 16 * (lch ^ vswz(i * RPL + lrow)), Vt + i * 64);
+        };
+        for (int pass = 0; pass <= kPos; ++pass) {
+        pm = pass == 0 ? 15u : 1u << (pass - 1);
+        f32x16 acc[D / 32];
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
+        float m = -3.402823466e38f, l = 0.f;   // finite: a position may have no entry in a block
+        // the tiles' last readers and the stores of the output rows are done (the
+        // waits below count the newest loads only)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if (nblk > 0) {
+            rows(0);
+            load_k();
+            load_v();
+        }
+        for (int blk = 0; blk < nblk; ++blk) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");   // K of this block (V may be in flight)
+            f32x16 sc;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < D / 16; ++ks)
+                sc = mfma_32x32x16(Kt[l32 * DC + ((2 * ks + g) ^ causal_kswz<D>(l32))], qop[ks], sc);
+            const bool more = blk + 1 < nblk;   // uniform
+            uint32_t mk[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mk[i] = masks[blk * 8 + 2 * i + g];
+            // the operand reads are complete: the next K may land
+            wave_lds_sync();
+            if (more) {
+                rows(blk + 1);
+                load_k();
             }
-        }
-        u32x4 ka[MAXB][D / 32];
+            float cm = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < MAXB; ++i) {
-            const int kb = w + 4 * i;
-            const int kr = kb < KB ? s_keys[kb * 16 + l16] : -1;
-            const uint16_t* krow = K + (gather_ok(kr) ? kv_row(p, b, kr, kvh) : 0);
+            for (int e = 0; e < 16; ++e) {
+                sc[e] = (mk[e >> 2] >> (8 * (e & 3))) & bit ? sc[e] : -INFINITY;
+                cm = fmaxf(cm, sc[e]);
+            }
+            cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+            const float mn = fmaxf(m, cm);
+            const float alpha = __builtin_amdgcn_exp2f((m - mn) * sl2);
+            const float mo = mn * sl2;
+            float rs = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < D / 32; ++ks)
-                ka[i][ks] = gather_ok(kr) ? *reinterpret_cast<const u32x4*>(krow + 32 * ks + 8 * q4) : zero;
-        }
-        const size_t qrow = (((size_t)b * p.T + u0 + pp) * p.H_q + kvh * G + hh) * D;
-        u32x4 qop[D / 32];
+            for (int e = 0; e < 16; ++e) {
+                sc[e] = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, -mo));
+                rs += sc[e];
+            }
+            rs += __shfl_xor(rs, 32, 64);
+            l = l * alpha + rs;
+            if (__builtin_amdgcn_ballot_w64(mn != m)) {
 #pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks)
-            qop[ks] = col_ok ? *reinterpret_cast<const u32x4*>(Q + qrow + 32 * ks + 8 * q4) : zero;
-        // V^T of the union into LDS
-        uint32_t* Vw = reinterpret_cast<uint32_t*>(Vt);
+                for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int r = 0; r < MAXR; ++r) {
-            const int it = tid + 256 * r;
-            if (it < (UP / 2) * DC) {
-                const int pr = it % (UP / 2), dc = it / (UP / 2), k0 = 2 * pr;
+                    for (int e = 0; e < 16; ++e) acc[db][e] *= alpha;
+            }
+            m = mn;
+            if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");   // V of this block
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int d = 8 * dc + i;
-                    Vw[(d * SC + ((k0 >> 3) ^ (d & swm))) * 4 + ((k0 & 7) >> 1)] = pair_word(va[r], vc[r], i);
+            for (int s = 0; s < 2; ++s) {
+                const u32x4 pf = {pack_bf16x2(sc[8 * s], sc[8 * s + 1]), pack_bf16x2(sc[8 * s + 2], sc[8 * s + 3]),
+                                  pack_bf16x2(sc[8 * s + 4], sc[8 * s + 5]), pack_bf16x2(sc[8 * s + 6], sc[8 * s + 7])};
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) {
+                    u32x2 va[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const int r = 16 * s + 8 * t + vrow;
+                        va[t] = read_tr16(Vt + r * DC + ((4 * db + vch) ^ vswz(r)), l16 & 1);
+                    }
+                    acc[db] = mfma_32x32x16(u32x4{va[0].x, va[0].y, va[1].x, va[1].y}, pf, acc[db]);
                 }
             }
+            wave_lds_sync();   // the V operands are read: the next V may land
+            if (more) load_v();
         }
-        // scores^T[key][column], masked per column to its position's entries
-        f32x4 sc[MAXB];
-        float mx = -INFINITY;
+        if (pass == 0) {
+            float t = 0.f;   // NaN when an accumulator is not finite
 #pragma unroll
-        for (int i = 0; i < MAXB; ++i) {
-            const int kb = w + 4 * i;
-            sc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (kb < KB) {
+            for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-                for (int ks = 0; ks < D / 32; ++ks) sc[i] = mfma_16x16x32(ka[i][ks], qop[ks], sc[i]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = kb * 16 + 4 * q4 + j, kv = s_keys[e];
-                    const bool ok = col_ok && kv >= 0 && kv <= u0 + pp && ((s_mask[e] >> pp) & 1);
-                    sc[i][j] = ok ? sc[i][j] : -INFINITY;
-                    mx = fmaxf(mx, sc[i][j]);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sc[i][j] = -INFINITY;
-            }
+                for (int e = 0; e < 16; ++e) t = fmaf(acc[db][e], 0.f, t);
+            if (__any(t != t)) continue;   // position by position
         }
-        // softmax over the union, per column (lane column l16)
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        if (q4 == 0) red[w * 16 + l16] = mx;
-        __syncthreads();
-        mx = fmaxf(fmaxf(red[l16], red[16 + l16]), fmaxf(red[32 + l16], red[48 + l16]));
-        float sum = 0.f;
+        // O rows through the K tile: row = column, chunk c at c ^ causal_kswz
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
 #pragma unroll
-        for (int i = 0; i < MAXB; ++i)
+        for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float e = sc[i][j] == -INFINITY ? 0.f : exp2f((sc[i][j] - mx) * sl2);
-                sc[i][j] = e;
-                sum += e;
+            for (int i = 0; i < 4; ++i) {
+                const int c = (4 * db + i) ^ causal_kswz<D>(l32);
+                reinterpret_cast<u32x2*>(Kt + l32 * DC + c)[g] =
+                    u32x2{pack_bf16x2(acc[db][4 * i] * inv, acc[db][4 * i + 1] * inv),
+                          pack_bf16x2(acc[db][4 * i + 2] * inv, acc[db][4 * i + 3] * inv)};
             }
-        sum += __shfl_xor(sum, 16, 64);
-        sum += __shfl_xor(sum, 32, 64);
-        __syncthreads();   // every wave has read the maxima
-        if (q4 == 0) red[w * 16 + l16] = sum;
-        __syncthreads();
-        sum = red[l16] + red[16 + l16] + red[32 + l16] + red[48 + l16];
-        const float inv = sum > 0.f ? 1.0f / sum : 0.f;
-        uint32_t* Pw = reinterpret_cast<uint32_t*>(Pl);
+        wave_lds_sync();
 #pragma unroll
-        for (int i = 0; i < MAXB; ++i) {
-            const int kb = w + 4 * i;
-            if (kb < KB) {
-                const int ch = (2 * kb + (q4 >> 1)) ^ (l16 & swm);
-                const int base = (l16 * SC + ch) * 4 + 2 * (q4 & 1);
-                Pw[base] = pack_bf16x2(sc[i][0] * inv, sc[i][1] * inv);
-                Pw[base + 1] = pack_bf16x2(sc[i][2] * inv, sc[i][3] * inv);
-            }
+        for (int i = 0; i < NL; ++i) {
+            const int r = i * RPL + lrow, po = r / G, ho = r - po * G;
+            const u32x4 v = Kt[r * DC + (lch ^ causal_kswz<D>(r))];
+            if (po < kPos && u0 + po < p.T && ((pm >> po) & 1))
+                *reinterpret_cast<u32x4*>(O + (((size_t)b * p.T + u0 + po) * p.H_q + kvh * G + ho) * D + 8 * lch) = v;
         }
-        __syncthreads();
-        // O^T[d][column] = V_union^T . P^T, d blocks db = w, w+4, ...
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) {
-            const int db = w + 4 * i;
-            const int dr = 16 * db + l16;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            for (int ks = 0; ks < UP / 32; ++ks) {
-                const u32x4 a = Vt[dr * SC + ((4 * ks + q4) ^ (dr & swm))];
-                const u32x4 bb = Pl[l16 * SC + ((4 * ks + q4) ^ (l16 & swm))];
-                acc = mfma_16x16x32(a, bb, acc);
-            }
-            if (col_ok && ((store_mask >> pp) & 1)) {
-                const u32x2 o2 = {pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
-                *reinterpret_cast<u32x2*>(O + qrow + 16 * db + 4 * q4) = o2;
-            }
+        if (pass == 0) break;
         }
-        __syncthreads();   // V^T and P are rewritten for the next KV head
+        load_q(kvh + WPG);
     }
-    }   // pass
 }
 
 // V transposed for the causal kernel: vt[b][kvh][d][t] (t < replay_tpad(T),
@@ -764,10 +1024,6 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // each 16-key group in the matching order (keys 0-3, 8-11, 4-7, 12-15), so k
 // step s of the product takes accumulator elements 8 (s % 2) .. +7 of block
 // s / 2 as its B operand.  LDS: K chunk [64][D], V^T chunk [D][64] (bf16).
-template <int D>
-__device__ __forceinline__ int causal_kswz(int r) {   // K rows: D/8 chunks
-    return D == 128 ? (r & 15) : ((r >> 1) & 7);
-}
 
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
@@ -932,20 +1188,34 @@ __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
     }
 }
 
-constexpr int kSelCacheMax = 15872;   // rows up to this length keep their keys in LDS (<= 64 KB with the counts)
-
 }  // namespace
 
 hipError_t launch_topS_select(const float* A, int32_t* idx, int B, int T, int S, hipStream_t stream) {
     if (B == 0 || T == 0) return hipSuccess;
     const dim3 grid(T, B);
-    const size_t counts = (size_t)2 * ((T >> 6) + 1) * 4;
-    if (T <= kSelCacheMax)
-        hipLaunchKernelGGL(k_topS_select<true>, grid, dim3(256), (size_t)T * 4 + counts, stream, A, idx, T, S);
-    else
-        hipLaunchKernelGGL(k_topS_select<false>, grid, dim3(256), counts, stream, A, idx, T, S);
+    const auto lds = [&](int q) { return (size_t)2 * (T / (64 * q) + 4) * sizeof(int); };
+    // the row in registers up to 16 pieces per thread
+    if (T <= 8192) hipLaunchKernelGGL(k_topS_select<RegKeys<8>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    else if (T <= 16384) hipLaunchKernelGGL(k_topS_select<RegKeys<16>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    else hipLaunchKernelGGL(k_topS_select<RowKeys>, grid, dim3(256), lds(1), stream, A, idx, T, S);
     return hipGetLastError();
 }
+
+namespace {
+
+// as many waves on a group as it has KV heads (1, 2 or 4), so none idles
+template <int D>
+hipError_t launch_sparse_group(const ReplayProblem& p, hipStream_t stream) {
+    const int64_t groups = (int64_t)p.B * ((p.T + kPos - 1) / kPos);
+    const int wpg = p.H_kv == 1 ? 1 : p.H_kv == 2 ? 2 : 4, gpw = 4 / wpg;
+    const dim3 grid(xcd_grid((int)((groups + gpw - 1) / gpw)));
+    if (wpg == 1) hipLaunchKernelGGL((k_sparse_attn_group<D, 1>), grid, dim3(256), 0, stream, p);
+    else if (wpg == 2) hipLaunchKernelGGL((k_sparse_attn_group<D, 2>), grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((k_sparse_attn_group<D, 4>), grid, dim3(256), 0, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
     if (p.B == 0 || p.T == 0) return hipSuccess;
@@ -953,12 +1223,9 @@ hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
         // the caller's check admits only these sizes; the register arrays of
         // the instantiation below cover every admitted S
         if (!replay_sparse_supported(p.D, p.S)) return hipErrorInvalidValue;
-        if (replay_sparse_pair_supported(p.D, p.S, p.H_q / p.H_kv)) {
-            const dim3 pgrid(xcd_grid((p.T + 1) / 2), p.B);
-            if (p.D == 128) hipLaunchKernelGGL(k_sparse_attn_pair<128>, pgrid, dim3(256), 0, stream, p);
-            else hipLaunchKernelGGL(k_sparse_attn_pair<64>, pgrid, dim3(256), 0, stream, p);
-            return hipGetLastError();
-        }
+        if (replay_sparse_group_supported(p.D, p.S, p.H_q / p.H_kv) &&
+            replay_causal_supported(p.T, p.H_kv, p.D, p.kv_layout == MOT_LAYOUT_BTHD))
+            return p.D == 128 ? launch_sparse_group<128>(p, stream) : launch_sparse_group<64>(p, stream);
         const dim3 grid(xcd_grid(p.T), p.B);
         const size_t lds = replay_sparse_lds_bytes(p.D, p.S);
         // register arrays sized for S <= 128, or for the largest S the LDS allows

@@ -1,0 +1,130 @@
+"""Selection from registers and the four-position sparse attention at the edges
+of their tiles, against torch in double on the CPU."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_28979_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+
+def _select(A, S):
+    """Top-S key sets by a stable sort: larger first, ties to the lower position."""
+    B, T, _ = A.shape
+    out = torch.full((B, T, S), -1, dtype=torch.int32)
+    for b in range(B):
+        for u in range(T):
+            row = A[b, u, :u + 1]
+            got = torch.sort(row, descending=True, stable=True).indices[:S].sort().values
+            out[b, u, :len(got)] = got.int()
+    return out
+
+
+def _attend(q, k, v, idx):
+    """o[b][u][h] over the entries of idx[b][u] in 0..u as listed (duplicates count)."""
+    B, T, H, D = q.shape
+    G = H // k.shape[2]
+    q, k, v = q.double(), k.double(), v.double()
+    o = torch.zeros(B, T, H, D, dtype=torch.float64)
+    for b in range(B):
+        for u in range(T):
+            n = idx[b, u][(idx[b, u] >= 0) & (idx[b, u] <= u)].long()
+            if len(n) == 0:
+                continue
+            kk, vv = (x[b, n].repeat_interleave(G, 1) for x in (k, v))
+            p = torch.softmax(torch.einsum("hd,nhd->hn", q[b, u], kk) / D ** 0.5, -1)
+            o[b, u] = torch.einsum("hn,nhd->hd", p, vv)
+    return o
+
+
+# T around the pieces (1024 positions) and their 16-byte alignment, S above and
+# below 256 (the lower bound), S = 1, and rows longer than the registers hold
+@pytest.mark.parametrize("T,S", [(1030, 32), (1029, 300), (2051, 256), (1100, 1), (8196, 64), (16388, 32)])
+def test_select_edges(T, S):
+    print("case", T, S, flush=True)
+    g = torch.Generator().manual_seed(T)
+    rows = sorted({S, S + 1, 1023, 1024, 1025, T // 2, T - 2, T - 1} & set(range(T)))
+    A = torch.zeros(1, T, T, device="cuda")
+    want = {}
+    for i, u in enumerate(rows):
+        r = torch.randn(T, generator=g)
+        if i % 4 == 1:
+            r = torch.round(r * 4) / 4                       # heavy ties
+        if i % 4 == 2:
+            r[torch.randperm(T, generator=g)[:T // 2]] = -torch.inf
+            r[5] = torch.inf
+        if i % 4 == 3:
+            r = torch.where(r > 0, r * 1e-30, torch.finfo(torch.float32).min)   # lowest values, tiny ones
+        r[u + 1:] = 7.0                                      # never chosen
+        A[0, u] = r
+        want[u] = torch.sort(r[:u + 1], descending=True, stable=True).indices[:S].sort().values.int()
+    idx = torch.full((1, T, S), -9, dtype=torch.int32, device="cuda")
+    mb.topS_select(A, idx, 1, T, S)
+    torch.cuda.synchronize()
+    for u, w in want.items():
+        got = idx[0, u].cpu()
+        assert torch.equal(got[:len(w)], w) and (got[len(w):] == -1).all(), u
+
+
+# KV heads 1, 2, 3, 4 and 8 (one, two and four waves per group; a wave with two
+# heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V, sets
+# past 128, and lists that are unordered, repeat keys or hold none
+ATTN = [(1, 37, 7, 1, 128, 32, 0), (2, 38, 4, 2, 64, 64, 1), (1, 39, 24, 3, 128, 96, 0), (1, 90, 28, 4, 128, 160, 1),
+        (3, 41, 8, 8, 64, 256, 0), (1, 1, 4, 4, 128, 32, 0)]
+
+
+@pytest.mark.parametrize("case", ATTN, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("kind", ["selected", "listed"])
+def test_attention_groups(case, kind):
+    B, T, Hq, Hkv, D, S, lay = case
+    print("case", case, kind, flush=True)
+    g = torch.Generator().manual_seed(S + T)
+    q, k, v = (torch.randn(B, T, h, D, generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
+    if kind == "selected":
+        idx = _select(torch.randn(B, T, T, generator=g), S)
+    else:   # any order, repeats, entries past u, -1 anywhere; some positions with nothing
+        idx = torch.randint(-2, T + 3, (B, T, S), generator=g).int()
+        idx[:, ::5] = -1
+    dev = [x.transpose(1, 2).contiguous().cuda() if lay and i else x.cuda() for i, x in enumerate((q, k, v))]
+    o = torch.full((B, T, Hq, D), -3.75, dtype=torch.bfloat16, device="cuda")
+    mb.replay_attention(*dev, idx.cuda(), o, B, T, Hq, Hkv, D, S=S, kv_layout=lay)
+    torch.cuda.synchronize()
+    ref = _attend(q, k, v, idx)
+    d = (o.cpu().double() - ref)
+    # bf16 probabilities and outputs: 2^-9 of the row's scale each
+    assert d.norm() <= 2.0 ** -7 * ref.norm()
+    assert d.abs().max() <= 2.0 ** -6 * max(1.0, ref.abs().max().item())
+    if kind == "listed":
+        assert (o[:, ::5] == 0).all()
+    again = torch.empty_like(o)
+    mb.replay_attention(*dev, idx.cuda(), again, B, T, Hq, Hkv, D, S=S, kv_layout=lay)
+    assert torch.equal(o, again)
+
+
+def test_attention_value_rows_that_are_not_finite():
+    """NaN and infinite value rows reach exactly the positions that attend them; their
+    group's other positions come out as without them."""
+    T, S, D, H = 64, 32, 128, 4
+    g = torch.Generator().manual_seed(3)
+    q, k, v = (torch.randn(1, T, h, D, generator=g).bfloat16() for h in (H, 2, 2))
+    idx = _select(torch.randn(1, T, T, generator=g), S)
+    idx[idx == 20] = 19          # (a repeat where 19 is in the set as well)
+    idx[idx == 40] = 39
+    idx[0, 33, 0], idx[0, 50, 1] = 20, 40
+    outs = []
+    for poke in (False, True):
+        w = v.clone()
+        if poke:
+            w[0, 20, 0], w[0, 40, 1, 7] = float("nan"), float("inf")
+        o = torch.empty(1, T, H, D, dtype=torch.bfloat16, device="cuda")
+        mb.replay_attention(q.cuda(), k.cuda(), w.cuda(), idx.cuda(), o, 1, T, H, 2, D, S=S)
+        outs.append(o.cpu().float()[0])
+    clean, got = outs
+    assert torch.isnan(got[33, :2]).all()                                # KV head 0's query heads
+    assert torch.isposinf(got[50, 2:, 7]).all()
+    same = torch.ones(T, H, D, dtype=torch.bool)
+    same[33, :2], same[50, 2:, 7] = False, False
+    # repeats make both runs walk the sets as listed, or one by one: the same sums
+    # in another order
+    assert (clean - got)[same].abs().max() <= 2.0 ** -7 * max(1.0, clean.abs().max().item())
