@@ -19,8 +19,7 @@
 //   the gathered key rows loaded straight into A operands, a softmax over the
 //   set, and O^T = V_sel^T . P^T with V_sel staged transposed in LDS.
 // * k_causal_attn: the full causal attention of the bottom layers, tiled
-//   (128 query positions of one head, two tiles per workgroup paired short
-//   with long, 64-key chunks of K and V^T loaded straight into LDS one chunk
+//   (tiles of 128 query positions of one head, 64-key chunks of K and V^T loaded straight into LDS one chunk
 //   ahead, online softmax, v_mfma_f32_32x32x16_bf16).
 // Scores, softmax and accumulation are fp32; Q, K, V, O are bf16.
 #include "mot_device.h"
@@ -1010,10 +1009,19 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
     }
 }
 
-// grid xcd_grid(npairs * H_q * B) with npairs = ceil(ceil(T/128) / 2), items
-// ordered (pair, head, batch row) pair fastest; 256 threads: query positions
-// u0 + 32w + l32 of head hq for two query tiles of 128 (a short and a long
-// one); 64-key chunks up to the tile's last position.
+// 256 threads; 128 query positions of one head per tile, 64-key chunks up to the
+// tile's last position.  Workgroups go to the 8 XCDs round-robin, and every XCD
+// takes a contiguous share of the heads (the heads of a KV group meet in one L2).
+//
+// causal_paired: a workgroup runs a short and a long tile, so that all do the same
+// work.  Grid xcd_grid(pairs * H_q * B), pairs fastest.  Otherwise one tile per
+// workgroup, an XCD's share of the (head, tile mod 8) in octets of tiles from the
+// longest down.  Grid 8 * H_q * B * ceil(tiles / 8).  Pairs are better where they
+// fill one round of the chip (512 workgroups) nearly exactly, and in launches of
+// many rounds; elsewhere their last round leaves CUs idle.  28 heads on 4 of 128,
+// pairs against single tiles: T = 2500 102 / 75 us, 3524 134 / 133, 4548 (504
+// pairs) 177 / 189, 7108 473 / 393; 2 x 3268 198 / 194, 2 x 5060 449 / 412, 2 x
+// 8132 (1792 pairs) 985 / 977; the backbone's 448 heads of 2048 663 / 700 to 850.
 //
 // Per wave and chunk, on v_mfma_f32_32x32x16_bf16: scores^T[key][position]
 // for two 32-key blocks (A = K rows from LDS, B = the wave's 32 query rows,
@@ -1025,6 +1033,11 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // step s of the product takes accumulator elements 8 (s % 2) .. +7 of block
 // s / 2 as its B operand.  LDS: K chunk [64][D], V^T chunk [D][64] (bf16).
 
+__host__ __device__ inline bool causal_paired(const ReplayProblem& p) {
+    const int64_t pairs = (int64_t)((p.T + 127) / 128 + 1) / 2 * p.H_q * p.B;
+    return pairs >= 4 * 512 || (pairs > 400 && pairs <= 512);
+}
+
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
     constexpr int DC = D / 8;
@@ -1033,12 +1046,23 @@ __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
     // then V^T rows (d: chunk c at c ^ ((d >> 1) & 7)); filled straight from
     // global memory (buffer loads into LDS) one chunk ahead
     __shared__ u32x4 lds[2 * (KS + VS)];
-    // workgroup x runs query tile x and tile ntiles-1-x: every workgroup
-    // walks about the same number of key chunks
-    const int ntiles = (p.T + 127) / 128, npairs = (ntiles + 1) / 2;
-    const int item = xcd_item(blockIdx.x, npairs * p.H_q * p.B);
-    if (item >= npairs * p.H_q * p.B) return;   // uniform over the workgroup
-    const int px = item % npairs, hq = (item / npairs) % p.H_q, b = item / (npairs * p.H_q);
+    const int ntiles = (p.T + 127) / 128, nh = p.H_q * p.B;
+    int head, tile0, tile1;   // tile1 < 0: one tile
+    if (causal_paired(p)) {
+        const int npairs = (ntiles + 1) / 2, item = xcd_item(blockIdx.x, npairs * nh);
+        if (item >= npairs * nh) return;   // uniform over the workgroup
+        head = item / npairs;
+        tile0 = item % npairs;
+        tile1 = ntiles - 1 - tile0;
+        if (tile1 <= tile0) tile1 = -1;
+    } else {
+        const int slot = blockIdx.x >> 3, c = (blockIdx.x & 7) * nh + slot % nh;
+        head = c >> 3;
+        tile0 = ntiles - 1 - (8 * (slot / nh) + (c & 7));
+        tile1 = -1;
+        if (tile0 < 0) return;   // uniform over the workgroup
+    }
+    const int hq = head % p.H_q, b = head / p.H_q;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l32 = lane & 31, g = lane >> 5;
     const int G = p.H_q / p.H_kv, kvh = hq / G;
     const uint16_t* Q = reinterpret_cast<const uint16_t*>(p.q);
@@ -1082,8 +1106,8 @@ __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
         asm volatile("" ::: "memory");
     };
     for (int pass = 0; pass < 2; ++pass) {
-    const int tile = pass == 0 ? px : ntiles - 1 - px;
-    if (pass == 1 && tile <= px) break;   // uniform over the workgroup
+    const int tile = pass == 0 ? tile0 : tile1;
+    if (tile < 0) break;   // uniform over the workgroup
     const int u0 = tile * 128;
     const int uw = u0 + 32 * w;            // first position of this wave
     const int u = uw + l32;                // this lane's query column
@@ -1244,8 +1268,8 @@ hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
         const dim3 tgrid((unsigned)(replay_tpad(p.T) / 64), p.H_kv, p.B);
         if (p.D == 128) hipLaunchKernelGGL(k_transpose_v<128>, tgrid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k_transpose_v<64>, tgrid, dim3(256), 0, stream, p);
-        const int npairs = ((p.T + 127) / 128 + 1) / 2;
-        const dim3 grid(xcd_grid(npairs * p.H_q * p.B));
+        const int ntiles = (p.T + 127) / 128, nh = p.H_q * p.B;
+        const dim3 grid(causal_paired(p) ? xcd_grid((ntiles + 1) / 2 * nh) : 8 * nh * ((ntiles + 7) / 8));
         if (p.D == 128) hipLaunchKernelGGL(k_causal_attn<128>, grid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k_causal_attn<64>, grid, dim3(256), 0, stream, p);
     }

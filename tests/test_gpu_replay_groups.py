@@ -128,3 +128,23 @@ def test_attention_value_rows_that_are_not_finite():
     # repeats make both runs walk the sets as listed, or one by one: the same sums
     # in another order
     assert (clean - got)[same].abs().max() <= 2.0 ** -7 * max(1.0, clean.abs().max().item())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_causal_tile_orders_agree(D):
+    """Launches of many rounds run a short and a long tile per workgroup, others one
+    tile each: the same bits."""
+    B, T, Hq, Hkv = 36, 261, 32, 4   # 3 tiles (an unpaired one); 2304 pairs of tiles
+    g = torch.Generator().manual_seed(9)
+    q, k, v = (torch.randn(B, T, h, D, generator=g).bfloat16().cuda() for h in (Hq, Hkv, Hkv))
+    whole = torch.full((B, T, Hq, D), -3.75, dtype=torch.bfloat16, device="cuda")
+    mb.replay_attention(q, k, v, None, whole, B, T, Hq, Hkv, D)
+    for b in (0, 17, B - 1):
+        one = torch.full((1, T, Hq, D), -3.75, dtype=torch.bfloat16, device="cuda")
+        mb.replay_attention(q[b:b + 1], k[b:b + 1], v[b:b + 1], None, one, 1, T, Hq, Hkv, D)
+        assert torch.equal(whole[b], one[0])
+    ref = torch.nn.functional.scaled_dot_product_attention(
+        *(x[:1].cpu().double().transpose(1, 2).repeat_interleave(Hq // x.shape[2], 1) for x in (q, k, v)),
+        is_causal=True).transpose(1, 2)
+    d = whole[:1].cpu().double() - ref
+    assert d.norm() <= 2.0 ** -7 * ref.norm()
