@@ -14,7 +14,7 @@
 //   (grouped-query: query head h reads KV head h / G), four positions and one
 //   KV head per wave over the union of the positions' sets, for G <= 8.
 // * k_sparse_attn: the same for one position (more than 8 query heads per KV
-//   head, or K of 2 GiB and more per batch row).  Per KV head the
+//   head, K of 2 GiB and more per batch row, small calls on few KV heads).  Per KV head the
 //   workgroup computes scores^T = K_sel . Q^T on v_mfma_f32_16x16x32_bf16 with
 //   the gathered key rows loaded straight into A operands, a softmax over the
 //   set, and O^T = V_sel^T . P^T with V_sel staged transposed in LDS.
@@ -1227,14 +1227,16 @@ hipError_t launch_topS_select(const float* A, int32_t* idx, int B, int T, int S,
 
 namespace {
 
-// as many waves on a group as it has KV heads (1, 2 or 4), so none idles
+// Two groups per workgroup when a group has work for two waves at most and there
+// are groups enough; else one, whose four waves build its list side by side (12
+// query heads on 2 of 128, one and two groups per workgroup: 129 positions 20 /
+// 27 us, 1040 29 / 34, 2080 47 / 41, 4000 63 / 55; with the selection)
 template <int D>
 hipError_t launch_sparse_group(const ReplayProblem& p, hipStream_t stream) {
     const int64_t groups = (int64_t)p.B * ((p.T + kPos - 1) / kPos);
-    const int wpg = p.H_kv == 1 ? 1 : p.H_kv == 2 ? 2 : 4, gpw = 4 / wpg;
+    const int wpg = p.H_kv <= 2 && groups > 400 ? 2 : 4, gpw = 4 / wpg;
     const dim3 grid(xcd_grid((int)((groups + gpw - 1) / gpw)));
-    if (wpg == 1) hipLaunchKernelGGL((k_sparse_attn_group<D, 1>), grid, dim3(256), 0, stream, p);
-    else if (wpg == 2) hipLaunchKernelGGL((k_sparse_attn_group<D, 2>), grid, dim3(256), 0, stream, p);
+    if (wpg == 2) hipLaunchKernelGGL((k_sparse_attn_group<D, 2>), grid, dim3(256), 0, stream, p);
     else hipLaunchKernelGGL((k_sparse_attn_group<D, 4>), grid, dim3(256), 0, stream, p);
     return hipGetLastError();
 }
@@ -1247,7 +1249,12 @@ hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
         // the caller's check admits only these sizes; the register arrays of
         // the instantiation below cover every admitted S
         if (!replay_sparse_supported(p.D, p.S)) return hipErrorInvalidValue;
-        if (replay_sparse_group_supported(p.D, p.S, p.H_q / p.H_kv) &&
+        // small calls on one or two KV heads stay with a position per workgroup: a
+        // group's list costs more latency than the shared gathers save (12 query
+        // heads on 2 of 128, with the selection: 129 positions 18 us against 20, 520
+        // 24 / 24, 780 31 / 25; on 2 of 64, 520 positions 18 / 22, 1040 25 / 26)
+        const bool small = p.H_kv <= 2 && (int64_t)p.B * p.T * p.H_kv * p.D <= 128 * 1024;
+        if (!small && replay_sparse_group_supported(p.D, p.S, p.H_q / p.H_kv) &&
             replay_causal_supported(p.T, p.H_kv, p.D, p.kv_layout == MOT_LAYOUT_BTHD))
             return p.D == 128 ? launch_sparse_group<128>(p, stream) : launch_sparse_group<64>(p, stream);
         const dim3 grid(xcd_grid(p.T), p.B);

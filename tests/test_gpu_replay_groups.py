@@ -67,11 +67,13 @@ def test_select_edges(T, S):
         assert torch.equal(got[:len(w)], w) and (got[len(w):] == -1).all(), u
 
 
-# KV heads 1, 2, 3, 4 and 8 (one, two and four waves per group; a wave with two
-# heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V, sets
-# past 128, and lists that are unordered, repeat keys or hold none
+# KV heads 1, 2, 3, 4 and 8 (one position per workgroup; two groups of two waves,
+# one of them idle or not, and an odd number of groups; one group of four; a wave
+# with two heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V,
+# sets past 128, and lists that are unordered, repeat keys or hold none
 ATTN = [(1, 37, 7, 1, 128, 32, 0), (2, 38, 4, 2, 64, 64, 1), (1, 39, 24, 3, 128, 96, 0), (1, 90, 28, 4, 128, 160, 1),
-        (3, 41, 8, 8, 64, 256, 0), (1, 1, 4, 4, 128, 32, 0)]
+        (3, 41, 8, 8, 64, 256, 0), (1, 1, 4, 4, 128, 32, 0), (9, 230, 7, 1, 128, 32, 0), (7, 237, 4, 2, 64, 64, 1),
+        (3, 1, 16, 2, 128, 32, 0), (5, 215, 3, 3, 64, 32, 1), (5, 220, 16, 2, 64, 32, 0)]
 
 
 @pytest.mark.parametrize("case", ATTN, ids=lambda c: "x".join(map(str, c)))
@@ -105,9 +107,9 @@ def test_attention_groups(case, kind):
 def test_attention_value_rows_that_are_not_finite():
     """NaN and infinite value rows reach exactly the positions that attend them; their
     group's other positions come out as without them."""
-    T, S, D, H = 64, 32, 128, 4
+    T, S, D, H = 64, 32, 128, 8
     g = torch.Generator().manual_seed(3)
-    q, k, v = (torch.randn(1, T, h, D, generator=g).bfloat16() for h in (H, 2, 2))
+    q, k, v = (torch.randn(1, T, h, D, generator=g).bfloat16() for h in (H, 4, 4))
     idx = _select(torch.randn(1, T, T, generator=g), S)
     idx[idx == 20] = 19          # (a repeat where 19 is in the set as well)
     idx[idx == 40] = 39
@@ -118,13 +120,13 @@ def test_attention_value_rows_that_are_not_finite():
         if poke:
             w[0, 20, 0], w[0, 40, 1, 7] = float("nan"), float("inf")
         o = torch.empty(1, T, H, D, dtype=torch.bfloat16, device="cuda")
-        mb.replay_attention(q.cuda(), k.cuda(), w.cuda(), idx.cuda(), o, 1, T, H, 2, D, S=S)
+        mb.replay_attention(q.cuda(), k.cuda(), w.cuda(), idx.cuda(), o, 1, T, H, 4, D, S=S)
         outs.append(o.cpu().float()[0])
     clean, got = outs
     assert torch.isnan(got[33, :2]).all()                                # KV head 0's query heads
-    assert torch.isposinf(got[50, 2:, 7]).all()
+    assert torch.isposinf(got[50, 2:4, 7]).all()
     same = torch.ones(T, H, D, dtype=torch.bool)
-    same[33, :2], same[50, 2:, 7] = False, False
+    same[33, :2], same[50, 2:4, 7] = False, False
     # repeats make both runs walk the sets as listed, or one by one: the same sums
     # in another order
     assert (clean - got)[same].abs().max() <= 2.0 ** -7 * max(1.0, clean.abs().max().item())
