@@ -1022,6 +1022,8 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // pairs against single tiles: T = 2500 102 / 75 us, 3524 134 / 133, 4548 (504
 // pairs) 177 / 189, 7108 473 / 393; 2 x 3268 198 / 194, 2 x 5060 449 / 412, 2 x
 // 8132 (1792 pairs) 985 / 977; the backbone's 448 heads of 2048 663 / 700 to 850.
+// Fewer than eight tiles leave empty workgroups in the octets, which many heads
+// notice (the backbone's 1792 heads of 63 positions: 463 / 489 us per call).
 //
 // Per wave and chunk, on v_mfma_f32_32x32x16_bf16: scores^T[key][position]
 // for two 32-key blocks (A = K rows from LDS, B = the wave's 32 query rows,
@@ -1034,8 +1036,9 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // s / 2 as its B operand.  LDS: K chunk [64][D], V^T chunk [D][64] (bf16).
 
 __host__ __device__ inline bool causal_paired(const ReplayProblem& p) {
-    const int64_t pairs = (int64_t)((p.T + 127) / 128 + 1) / 2 * p.H_q * p.B;
-    return pairs >= 4 * 512 || (pairs > 400 && pairs <= 512);
+    const int ntiles = (p.T + 127) / 128;
+    const int64_t nh = (int64_t)p.H_q * p.B, pairs = (ntiles + 1) / 2 * nh;
+    return pairs >= 4 * 512 || (pairs > 400 && pairs <= 512) || (ntiles < 8 && nh >= 128);
 }
 
 template <int D>
