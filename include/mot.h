@@ -75,6 +75,12 @@ typedef enum { MOT_ALGO_AUTO = 0, MOT_ALGO_UNFUSED = 1, MOT_ALGO_FUSED = 2, MOT_
  *                  unselected ones a gate of exactly zero.
  *   hidden         translator hidden width
  *   dtype          MOT_F32: fp32 storage and math (erf GELU, expf softmax).
+ *                  Where hidden % 64 == 0 and d_in % 16 == 0 the products are
+ *                  formed on the bf16 matrix cores from exact three-way splits
+ *                  of their operands, to 2^-33 of a product, and summed in fp32;
+ *                  results for which parts of operands or products leave bf16's
+ *                  or fp32's range (infinities, NaN, values near the least or
+ *                  the largest ones) are computed on the fp32 matrix cores.
  *                  MOT_BF16: bf16 storage; fp32 accumulation; fp32 gates;
  *                  tanh-form GELU (within 4.7e-4 absolute of the erf form);
  *                  the gate-scaled hidden activation is rounded to bf16
@@ -96,9 +102,9 @@ typedef enum { MOT_ALGO_AUTO = 0, MOT_ALGO_UNFUSED = 1, MOT_ALGO_FUSED = 2, MOT_
  *                  256 pairs), and for top_k > 1 a combine sums each token's
  *                  top_k rows (workspace needed); MOT_ALGO_UNFUSED = router,
  *                  then two grouped GEMMs over every translator through a
- *                  hidden-activation workspace (the fp32 matrix-core GEMMs,
- *                  used when hidden % 64 == 0, compute the router inside the
- *                  first one).  Requesting an impossible path
+ *                  hidden-activation workspace (the fp32 GEMMs on the matrix
+ *                  cores, see dtype, compute the router in the first one's
+ *                  launch).  Requesting an impossible path
  *                  returns MOT_ERR_UNSUPPORTED.  All paths compute the same
  *                  function.
  *   streams        2 (or 0): keys and values, each with its own translators;

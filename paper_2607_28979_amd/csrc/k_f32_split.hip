@@ -9,18 +9,21 @@
 //
 // Every fp32 operand x is split exactly into three bf16 values, x = h + m + l
 // (each the round-to-nearest of what is left: 8 + 8 + 8 significand bits), and
-// a product is six v_mfma_f32_32x32x16_bf16: hh, hm, mh, mm, hl, lh.  The terms
-// left out (ml, lm, ll) are below 2^-25 of a product.  hh has accumulators of
-// its own, the five small terms share another set, so the sum is rounded once
-// per 16 products (the fp32 matrix core rounds once per 4): against 64 bits the
-// result is closer than v_mfma_f32_16x16x4_f32 gives.  Six bf16 products cost
-// 6/16 of the fp32 matrix core's time for the same fp32 product.
+// a product is eight v_mfma_f32_32x32x16_bf16: hh, hm, mh, mm, hl, lh, ml, lm.
+// The term left out (ll) is below 2^-33 of a product.  hh has accumulators of
+// its own, the seven small terms share another set, so a product is rounded once
+// and a sum once per 16 products (the fp32 matrix core rounds once per 4): against
+// 64 bits the result is closer than v_mfma_f32_16x16x4_f32 gives.  Eight bf16
+// products cost half of the fp32 matrix core's time for the same fp32 product.
+// (Without ml and lm, six products, a single product was off by up to 0.89e-7
+// of itself instead of 0.60e-7.)
 //
-// The split needs finite operands below bf16's largest value (3.39e38).  Any
-// other operand makes the block's result non-finite, and a 32x32 block whose
-// result is not finite is computed again on v_mfma_f32_32x32x2_f32, so
-// infinities, NaN and overflow come out as plain fp32 gives them.  Parts below
-// 2^-126 of very small operands (under 1e-33) may be lost.
+// A 32x32 block is computed again on v_mfma_f32_32x32x2_f32 where the split does
+// not hold: where a result is not finite (operands above bf16's largest value,
+// 3.39e38; infinities, NaN and overflow come out as plain fp32 gives them), and
+// where one is so small beside its row's and column's largest operands that parts
+// of operands or products below bf16's or fp32's least value could count
+// (finish_block).
 //
 // Workgroup = 4 waves, TM (hidden or output) rows x TN tokens, K in steps of
 // 32: a thread fetches 8 consecutive fp32 of a row (a step ahead), splits them
@@ -28,10 +31,11 @@
 // c ^ ((r >> 2) & 3) (16 lanes reading one chunk of 16 rows touch 16 distinct
 // bank groups).
 //
-// Bound: latency at one token tile (64 tokens: 84.8 -> 42.6 us per call against
-// v_mfma_f32_16x16x4_f32 with operands straight from global memory), the sum of
-// splitting and MFMA issue at many (999 tokens: 698 -> 259 us, 146 TFLOP/s of
-// fp32 products).  Error against 64 bits, both sizes: 7.0e-7 -> 2.7e-7.
+// Bound: latency at one token tile (64 tokens: 84.8 -> 46.8 us per call against
+// v_mfma_f32_16x16x4_f32 with operands straight from global memory; 42.5 with six
+// products), the sum of splitting, LDS and MFMA issue at many (999 tokens: 698 ->
+// 318 us, 119 TFLOP/s of fp32 products; 266 with six products and without the row
+// maxima).  Error against 64 bits, both sizes: 7.0e-7 -> 2.7e-7.
 #include <type_traits>
 
 #include "mot_device.h"
@@ -49,6 +53,14 @@ __device__ __forceinline__ size_t src_off(const Problem& p, int i, int tok, int 
     if (p.src_layout == MOT_LAYOUT_BTHD) return layer + (size_t)tok * p.d_in + c;
     const int b = tok / p.T, t = tok % p.T, hh = c / p.D_src, dd = c % p.D_src;
     return layer + (((size_t)b * p.H_src + hh) * p.T + t) * p.D_src + dd;
+}
+
+// max(m, |x|, |y|), NaN left out, in one instruction (fmaxf of loaded values costs
+// three more, which quiet signalling NaN)
+__device__ __forceinline__ float max_abs(float m, float x, float y) {
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(x), "v"(y));
+    return r;
 }
 
 __device__ __forceinline__ void lds_barrier() {
@@ -70,7 +82,7 @@ struct Tile {
     static constexpr int MB = TM / WM / 32, NB = TN / WN / 32;
     static constexpr int IA = TM * 4 / 256, IB = TN * 4 / 256;   // 8-value items per thread and K step
     static constexpr int PLANE = (TM + TN) * 4;                  // 16-byte chunks of one part
-        static constexpr int LDS = STAGES * 3 * PLANE;
+    static constexpr int LDS = STAGES * 3 * PLANE;
     static_assert(WM * WN == 4 && TM % (WM * 32) == 0 && TN % (WN * 32) == 0, "four waves of 32x32 blocks");
     static_assert(STAGES == 1 || STAGES == 2, "forms of the K loop");
     static_assert(TM * 4 % 256 == 0 && TN * 4 % 256 == 0, "whole items per thread");
@@ -88,7 +100,23 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <class T>
 struct Acc {
     f32x16 hi[T::MB][T::NB], lo[T::MB][T::NB];
+    float big[T::IA + T::IB];   // largest magnitude this thread split of item q's row
 };
+
+// Row maxima of a tile (TM rows of A, then TN of B) from the threads' shares; ends
+// in a barrier
+template <class T>
+__device__ __forceinline__ void row_maxima(const Acc<T>& acc, float* s_max) {
+#pragma unroll
+    for (int q = 0; q < T::IA + T::IB; ++q) {
+        float v = acc.big[q];
+        v = fmaxf(v, __shfl_xor(v, 1, 64));
+        v = fmaxf(v, __shfl_xor(v, 2, 64));
+        const int row = (q < T::IA ? 0 : T::TM) + (threadIdx.x >> 2) + 64 * (q < T::IA ? q : q - T::IA);
+        if ((threadIdx.x & 3) == 0) s_max[row] = v;
+    }
+    __syncthreads();
+}
 
 // The K loop of one tile: acc[hi|lo][block] over nk steps of 32.  fetch_a(q,
 // v) and fetch_b(q, v) load this thread's item q (the 8 values of chunk tid % 4
@@ -97,10 +125,10 @@ struct Acc {
 // multiplied by when they are used.
 //
 // STAGES = 1, for launches that fill the chip: split the step into LDS, barrier,
-// products; three workgroups per CU overlap each other's phases.  (Slotting the
-// splitting between the MFMAs, below, measured 289 us against 274 us with 128 x
-// 64 tiles, and 128 x 128 tiles 294-334 us: 999 tokens, 768 -> 2 x 256 -> 768, 24
-// units.)
+// products; three workgroups per CU overlap each other's phases.  (With six
+// products, slotting the splitting between the MFMAs, below, measured 289 us
+// against 274 us with 128 x 64 tiles, and 128 x 128 tiles 294-334 us: 999 tokens,
+// 768 -> 2 x 256 -> 768, 24 units.)
 //
 // STAGES = 2, for few workgroups, where a CU holds one: a step is two halves (K
 // 0..15 and 16..31) of MFMA slots.  The barrier sits between the halves: before
@@ -109,13 +137,13 @@ struct Acc {
 // writing of step s + 2 begins, into the stage of step s.  The vector work of
 // splitting a step so spreads over a whole step's MFMAs: three stages per pair of
 // values (h and the remainder; m and the remainder; l), a fixed share of them in
-// each slot.  (64 tokens: 43.5 against 47.5 us with STAGES = 1.)
+// each slot.  (64 tokens, six products: 43.5 against 47.5 us with STAGES = 1.)
 //
 // Fetches past the last step repeat it; what is split from them is not used.
 template <class T, bool SCALED, class FA, class FB, class ADV>
 __device__ __forceinline__ void k_loop(u32x4* lds, int nk, FA fetch_a, FB fetch_b, ADV advance, Acc<T>& acc) {
     constexpr int MB = T::MB, NB = T::NB, NI = T::IA + T::IB, STAGE = 3 * T::PLANE;
-    constexpr int NM = 12 * MB * NB, H = NM / 2;   // MFMA slots of a step, of a half
+    constexpr int NM = 16 * MB * NB, H = NM / 2;   // MFMA slots of a step, of a half
     constexpr int NS = NI * 12, HS = NS / 2;       // splitting stages of a step, of a half
     constexpr int NR = 3 * (MB + NB);              // operand reads of a half
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 5, l32 = lane & 31;
@@ -126,6 +154,8 @@ __device__ __forceinline__ void k_loop(u32x4* lds, int nk, FA fetch_a, FB fetch_
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc.hi[a][b][e] = acc.lo[a][b][e] = 0.f;
+#pragma unroll
+    for (int q = 0; q < NI; ++q) acc.big[q] = 0.f;
 
     f32x4 raw[NI][2];
     float scale[T::IB];
@@ -150,6 +180,7 @@ __device__ __forceinline__ void k_loop(u32x4* lds, int nk, FA fetch_a, FB fetch_
                 rx *= scale[q - T::IA];
                 ry *= scale[q - T::IA];
             }
+            acc.big[q] = max_abs(acc.big[q], rx, ry);
             ph[pr] = pack_bf16x2(rx, ry);
             rx -= bf16_lo(ph[pr]);
             ry -= bf16_hi(ph[pr]);
@@ -181,7 +212,7 @@ __device__ __forceinline__ void k_loop(u32x4* lds, int nk, FA fetch_a, FB fetch_
     };
     auto mma = [&](auto ksc, auto kc) {   // slot k of half ks
         constexpr int ks = decltype(ksc)::value, k = decltype(kc)::value, t = k / (MB * NB), a = k / NB % MB, b = k % NB;
-        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+        constexpr int PA[8] = {0, 0, 1, 1, 0, 2, 1, 2}, PB[8] = {0, 1, 0, 1, 2, 0, 2, 1};
         f32x16& c = t == 0 ? acc.hi[a][b] : acc.lo[a][b];
         c = mfma_32x32x16(fa[ks][PA[t]][a], fb[ks][PB[t]][b], c);
     };
@@ -224,23 +255,39 @@ __device__ __forceinline__ void k_loop(u32x4* lds, int nk, FA fetch_a, FB fetch_
     }
 }
 
-// hi + lo of a block; where that is not finite anywhere in the wave's block, the
-// block again in plain fp32 (a(k), b(k): this lane's row and column operands)
+// hi + lo of a block, or, where the split does not hold for one of its elements,
+// the block in plain fp32.  a(k), b(k): 4 values at k of this lane's row and
+// column; row_max, col_max: the largest operand of each row, of this lane's column.
+//
+// A lost part of an operand is below 2^-125 (bf16 values under 2^-126 taken as
+// 0) and meets an operand of the other side; a lost product is below 2^-126, and
+// each of K has eight.  Against a result of at least 2^-93 K (1 + row_max +
+// col_max) all of them together are below 2^-29 of it.  Results of ordinary data
+// are far above that (1e-25 for operands around 1), but for exact zeros of rows or
+// columns of zeros, where nothing is lost.
 template <class FA, class FB>
-__device__ __forceinline__ f32x16 finish_block(const f32x16& hi, const f32x16& lo, int K, FA a, FB b) {
+__device__ __forceinline__ f32x16 finish_block(const f32x16& hi, const f32x16& lo, int K, const float* row_max,
+                                               float col_max, FA a, FB b) {
+    const int g = (threadIdx.x & 63) >> 5;
+    const float least = (float)K * 0x1p-93f;
     f32x16 v;
     bool bad = false;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         v[e] = hi[e] + lo[e];
-        bad |= !(fabsf(v[e]) <= 3.402823466e38f);
+        const float rm = row_max[8 * (e >> 2) + 4 * g + (e & 3)], mag = fabsf(v[e]);
+        bad |= !(mag <= 3.402823466e38f) || (mag < least * (1.0f + rm + col_max) && rm > 0.f && col_max > 0.f);
     }
     if (__any(bad)) {
-        const int g = (threadIdx.x & 63) >> 5;
 #pragma unroll
         for (int e = 0; e < 16; ++e) v[e] = 0.f;
+        // a step of 8: the lanes of half g hold k .. k+3 of their half
 #pragma unroll 1
-        for (int k = 0; k < K; k += 2) v = __builtin_amdgcn_mfma_f32_32x32x2f32(a(k + g), b(k + g), v, 0, 0, 0);
+        for (int k = 4 * g; k < K; k += 8) {
+            const f32x4 av = a(k), bv = b(k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], v, 0, 0, 0);
+        }
     }
     return v;
 }
@@ -328,6 +375,7 @@ __device__ __forceinline__ void router_tile(const Problem& p, uint32_t code, int
 template <class T, bool GENERAL>
 __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab ut) {
     __shared__ u32x4 s_lds[T::LDS];
+    __shared__ float s_max[T::TM + T::TN];
     static_assert(T::LDS >= 4 * 64 * 4, "the router's partial logits fit");
     const int EH = p.E * p.hidden, nA = (EH + T::TM - 1) / T::TM, d_in = p.d_in;
     const int nr = (p.n_tok + 63) / 64, per = nr + nA * ((p.n_tok + T::TN - 1) / T::TN);
@@ -393,6 +441,7 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab u
             in_seg = next ? 0 : in_seg;
         },
         acc);
+    row_maxima(acc, s_max);
 
     // epilogue: + b1, GELU; a lane holds hidden rows 8e + 4g .. +3 of the block
     // for token l32
@@ -403,12 +452,12 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab u
     for (int a = 0; a < T::MB; ++a)
 #pragma unroll
         for (int b = 0; b < T::NB; ++b) {
-            const int h0 = hid0 + (w % T::WM * T::MB + a) * 32, tok = tok0 + (w / T::WM * T::NB + b) * 32 + l32;
-            const int tokc = min(tok, p.n_tok - 1);
+            const int hr = (w % T::WM * T::MB + a) * 32, tc = (w / T::WM * T::NB + b) * 32 + l32;
+            const int h0 = hid0 + hr, tok = tok0 + tc, tokc = min(tok, p.n_tok - 1);
             const float* wrow = W1 + (size_t)min(h0 + l32, EH - 1) * d_in;
             const f32x16 s = finish_block(
-                acc.hi[a][b], acc.lo[a][b], d_in, [&](int k) { return wrow[k]; },
-                [&](int k) { return src[src_off(p, i, tokc, k)]; });
+                acc.hi[a][b], acc.lo[a][b], d_in, s_max + hr, s_max[T::TM + tc], [&](int k) { return ld4(wrow + k); },
+                [&](int k) { return ld4(src + src_off(p, i, tokc, k)); });
             if (tok >= p.n_tok) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -430,6 +479,7 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab u
 template <class T>
 __global__ __launch_bounds__(256, 3) void k_f32_split_gemm2(Problem p, UnitTab ut) {
     __shared__ u32x4 s_lds[T::LDS];
+    __shared__ float s_max[T::TM + T::TN];
     const int E = p.E, hidden = p.hidden, EH = E * hidden, d_out = p.d_out, nA = (d_out + T::TM - 1) / T::TM;
     const int per = nA * ((p.n_tok + T::TN - 1) / T::TN), item = xcd_item(ut.n * per);
     if (item >= ut.n * per) return;   // uniform over the workgroup
@@ -478,6 +528,7 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm2(Problem p, UnitTab u
             m += next ? 1 : 0;
         },
         acc);
+    row_maxima(acc, s_max);
 
     // epilogue: + sum_m g_m b2_m; a lane holds outputs 8e + 4g .. +3 of the
     // block for token l32
@@ -488,12 +539,19 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm2(Problem p, UnitTab u
     for (int a = 0; a < T::MB; ++a)
 #pragma unroll
         for (int b = 0; b < T::NB; ++b) {
-            const int o0 = out0 + (w % T::WM * T::MB + a) * 32, tok = tok0 + (w / T::WM * T::NB + b) * 32 + l32;
+            const int orel = (w % T::WM * T::MB + a) * 32, tc = (w / T::WM * T::NB + b) * 32 + l32;
+            const int o0 = out0 + orel, tok = tok0 + tc;
             const int tokc = min(tok, p.n_tok - 1), orow = min(o0 + l32, d_out - 1);
             const f32x16 y = finish_block(
-                acc.hi[a][b], acc.lo[a][b], EH,
-                [&](int k) { return W2[((size_t)(k / hidden) * d_out + orow) * hidden + k % hidden]; },
-                [&](int k) { return G[(size_t)tokc * E + k / hidden] * H[(size_t)tokc * EH + k]; });
+                acc.hi[a][b], acc.lo[a][b], EH, s_max + orel, s_max[T::TM + tc],
+                [&](int k) { return ld4(W2 + ((size_t)(k / hidden) * d_out + orow) * hidden + k % hidden); },
+                [&](int k) {
+                    const float gate = G[(size_t)tokc * E + k / hidden];
+                    f32x4 h = ld4(H + (size_t)tokc * EH + k);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) h[r] *= gate;
+                    return h;
+                });
             if (tok >= p.n_tok) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {

@@ -64,7 +64,7 @@ def test_split_products(shape):
     got, ref = _run(*shape)
     err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     print("  rel %.2e" % err, flush=True)
-    # exact products up to 2^-25 and fp32 sums of up to 1024 terms: below 1e-6
+    # products to 2^-33 and fp32 sums of up to 1024 terms: below 1e-6
     assert err < 1e-6
     assert np.abs(got - ref).max() < 2e-5 * np.sqrt(np.mean(ref ** 2))
 
@@ -91,11 +91,83 @@ def test_operands_outside_the_split(T):
         assert np.isnan(v[1][11]).all()
 
 
-def test_infinite_source_value():
-    """An infinite source value makes its token's row NaN and no other."""
+@pytest.mark.parametrize("heads", [(2, 32, 0), (3, 32, 1), (4, 20, 1)], ids=["bthd", "bhtd", "bhtd-20"])
+def test_infinite_source_value(heads):
+    """An infinite source value makes its token's row NaN and no other (the others of its
+    blocks are computed again from rows in either layout)."""
     def poke(d):
         d["z"][:, :, 0, 5, 0, 1] = np.inf
-    got, ref = _run(1, 40, 2, 32, 1, 64, 2, 128, poke=poke)
+    got, ref = _run(1, 40, heads[0], heads[1], 1, 64, 2, 128, layout=heads[2], poke=poke)
     assert np.isnan(got[:, :, 5]).all() and np.isnan(ref[:, :, 5]).all()
     rest = np.arange(40) != 5
     assert np.abs(got[:, :, rest] - ref[:, :, rest]).max() < 2e-5 * np.sqrt(np.mean(ref[:, :, rest] ** 2))
+
+
+def _linear(z, w1, w2):
+    """W2 (W1 z) of every unit (identity activation, one translator, whose gate is 1): z
+    [2][L][T][d_in], w1 [L][2][hidden][d_in], w2 [L][2][d_out][hidden]; [L][2][T][d_out]."""
+    import torch
+    _, L, T, di = z.shape
+    hidden, do = w1.shape[2], w2.shape[2]
+    dev = [torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda() for x in (*z, w1, w2)]
+    dst = [torch.full((L, 1, T, 1, do), -3.75, device="cuda") for _ in range(2)]
+    sh = mb.Shapes(L, L, 1, T, 1, di, 1, do, 1, hidden, dtype=mb.MOT_F32, act=mb.ACT_IDENTITY)
+    mb.translate(dev[0], dev[1], list(range(L)), dev[2], None, dev[3], None, torch.zeros(L, 2, 1, di, device="cuda"), None,
+                 *dst, sh)
+    torch.cuda.synchronize()
+    return np.stack([x.reshape(L, T, do).cpu().numpy() for x in dst], 1).astype(np.float64)
+
+
+# exponents of the weights and of the values: ordinary; parts of one operand below
+# bf16's least value; subnormal operands; products of ordinary operands whose small
+# parts fall below fp32's least value; both operands small
+EXPONENTS = [(0, 0), (-120, 100), (100, -124), (-126, 120), (-140, 120), (-60, -50), (-45, -70), (-110, 0)]
+
+
+@pytest.mark.parametrize("T", [40, 900])
+@pytest.mark.parametrize("exps", EXPONENTS, ids=lambda e: "%d,%d" % e)
+@pytest.mark.parametrize("layer", [1, 2])
+def test_single_products(T, exps, layer):
+    """Rows with one value that is not zero: every output is one fp32 product, rounded once."""
+    print("case", T, exps, layer, flush=True)
+    n, L = 64, 12 if T > 64 else 1
+    rng = np.random.default_rng(T + 7 * layer)
+
+    def draw(e, *shape):
+        return ((1 + rng.random(shape)) * rng.choice([-1, 1], shape) * 2.0 ** e).astype(np.float32)
+
+    z = np.zeros((2, L, T, n), np.float32)
+    t = np.arange(T)
+    z[:, :, t, (5 * t) % n] = draw(exps[1], 2, L, T)
+    w = draw(exps[0], L, 2, n, n)
+    eye = np.broadcast_to(np.eye(n, dtype=np.float32), w.shape)
+    got = _linear(z, w, eye) if layer == 1 else _linear(z, eye, w)
+    want = np.einsum("xltk,lxok->lxto", z.astype(np.float64), w.astype(np.float64))
+    # half a unit in the last place (the dropped term is 2^-33 of the product), of the
+    # least normal value where a product lies below it
+    bound = 2.0 ** -24 * np.maximum(np.abs(want) * 1.01, 2.0 ** -126)
+    err = np.abs(got - want)
+    print("  worst %.2e of the product" % (err / np.abs(want)).max(), flush=True)
+    assert (err <= bound).all()
+
+
+@pytest.mark.parametrize("T", [40, 900])
+def test_small_products_that_count(T):
+    """A tiny weight times a huge value beside ordinary terms of the same size, and sums
+    of tiny weights only: as near 64 bits as sums of ordinary values."""
+    n, L = 64, 12 if T > 64 else 1
+    rng = np.random.default_rng(T)
+    z, w = rng.standard_normal((2, L, T, n)), rng.standard_normal((L, 2, n, n))
+    z[..., 0] *= 2.0 ** 110
+    w[..., 0] *= 2.0 ** -118
+    z[..., 1:] *= 2.0 ** -8
+    z[:, :, 7] = 0                          # a row of zeros
+    w[:, :, 9] = rng.standard_normal((L, 2, n)) * 2.0 ** -117
+    z, w = z.astype(np.float32), w.astype(np.float32)
+    eye = np.broadcast_to(np.eye(n, dtype=np.float32), w.shape)
+    got = _linear(z, w, eye)
+    want = np.einsum("xltk,lxok->lxto", z.astype(np.float64), w.astype(np.float64))
+    mass = np.einsum("xltk,lxok->lxto", np.abs(z).astype(np.float64), np.abs(w).astype(np.float64))
+    # fp32 sums of 64 terms: below 64 roundings of half a unit of the terms' total
+    assert (np.abs(got - want) <= 64 * 2.0 ** -24 * mass).all()
+    assert (got[:, :, 7] == 0).all()
