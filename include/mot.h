@@ -339,9 +339,9 @@ size_t mot_replay_workspace_bytes(const mot_replay_shapes* shapes, int with_sets
  * the S positions v <= u with the largest A[b][u][v] (ties: lower v), written
  * in ascending order to idx[b][u][0..S) and padded with -1 (all of 0..u when
  * u < S).  A: device fp32 [B][T][T] head-averaged source attention (entries
- * v > u are not read); idx: device int32 [B][T][S].  Only B, T and S of
- * `shapes` are used (T at most 65536).  Both pointers 4-byte aligned and
- * non-overlapping.
+ * v > u have no influence; up to three of them, inside the row, may be read);
+ * idx: device int32 [B][T][S].  Only B, T and S of `shapes` are used (T at most
+ * 65536).  Both pointers 4-byte aligned and non-overlapping.
  */
 mot_status mot_topS_select(const float* A, int32_t* idx, const mot_replay_shapes* shapes, hipStream_t stream);
 

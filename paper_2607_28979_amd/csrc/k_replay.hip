@@ -74,8 +74,9 @@ struct RegKeys {
     int n;
     __device__ __forceinline__ void load(const float* row, int T, int n_) {
         n = n_;
-        const bool whole = (T & 3) == 0;   // rows are 16-byte aligned (T % 4 == 0): a
-        // piece may end past u, still inside the row; the rest is never used
+        // a row on a 16-byte boundary with T % 4 == 0 (uniform): a piece may end past
+        // u, still inside the row; the rest is never used
+        const bool whole = (T & 3) == 0 && (reinterpret_cast<uintptr_t>(row) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int v = 1024 * i + 4 * threadIdx.x;

@@ -67,6 +67,29 @@ def test_select_edges(T, S):
         assert torch.equal(got[:len(w)], w) and (got[len(w):] == -1).all(), u
 
 
+@pytest.mark.parametrize("T,off", [(1032, 1), (1032, 2), (8200, 3), (1032, 4)])
+def test_select_unaligned_base(T, off):
+    """A 4-byte aligned map at any offset from a 16-byte boundary (rows of T % 4 == 0
+    are fetched in 16-byte pieces only where they start on one)."""
+    S = 64
+    print("case", T, off, flush=True)
+    g = torch.Generator().manual_seed(off)
+    buf = torch.zeros(T * T + off, device="cuda")
+    A = buf[off:].view(1, T, T)
+    assert buf.data_ptr() % 16 == 0 and A.data_ptr() % 16 == 4 * off % 16
+    want = {}
+    for u in (S, 1023, 1026, T - 2, T - 1):
+        r = torch.randn(T, generator=g)
+        r[u + 1:] = 7.0
+        A[0, u] = r
+        want[u] = torch.sort(r[:u + 1], descending=True, stable=True).indices[:S].sort().values.int()
+    idx = torch.full((1, T, S), -9, dtype=torch.int32, device="cuda")
+    mb.topS_select(A, idx, 1, T, S)
+    torch.cuda.synchronize()
+    for u, w in want.items():
+        assert torch.equal(idx[0, u].cpu(), w), u
+
+
 # KV heads 1, 2, 3, 4 and 8 (one position per workgroup; two groups of two waves,
 # one of them idle or not, and an odd number of groups; one group of four; a wave
 # with two heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V,
