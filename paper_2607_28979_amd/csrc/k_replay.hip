@@ -872,7 +872,15 @@ __global__ __launch_bounds__(256, 2) void k_sparse_attn_group(ReplayProblem p) {
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
-        float m = -3.402823466e38f, l = 0.f;   // finite: a position may have no entry in a block
+        // the rounded exponent offset of a maximum (as a value of its own: contracted
+        // into the subtraction below it would not be rounded there)
+        auto offset = [&](float mx) {
+            float r = mx * sl2;
+            asm("" : "+v"(r));
+            return r;
+        };
+        // running maximum (finite: a position may have no entry in a block) and its offset
+        float m = -3.402823466e38f, mo = offset(m), l = 0.f;
         // the tiles' last readers and the stores of the output rows are done (the
         // waits below count the newest loads only)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -907,8 +915,12 @@ __global__ __launch_bounds__(256, 2) void k_sparse_attn_group(ReplayProblem p) {
             }
             cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
             const float mn = fmaxf(m, cm);
-            const float alpha = __builtin_amdgcn_exp2f((m - mn) * sl2);
-            const float mo = mn * sl2;
+            // between the rounded offsets: earlier blocks keep their weight against this
+            // one's exactly, however large the scores ((m - mn) sl2 is off by an offset's
+            // rounding: 6 % at scores of 2^23)
+            const float mon = offset(mn);
+            const float alpha = __builtin_amdgcn_exp2f(mo - mon);
+            mo = mon;
             float rs = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {

@@ -127,6 +127,25 @@ def test_attention_groups(case, kind):
     assert torch.equal(o, again)
 
 
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 28, 4), (64, 24, 8)])
+def test_attention_large_scores(D, Hq, Hkv):
+    """Scores near 2^23 (whole numbers, exact in fp32) that differ by a few units and grow
+    along the sets: the blocks of a set keep their weights against each other."""
+    T, S = 200, 128
+    g = torch.Generator().manual_seed(D)
+    q, k = torch.full((1, T, Hq, D), 256.0), torch.full((1, T, Hkv, D), 256.0 * 128 // D)
+    q[..., 0] = torch.randint(1, 4, (1, T, Hq), generator=g).float()
+    k[..., 0] = torch.randint(0, 9, (1, T, Hkv), generator=g) + (torch.arange(T) // 4)[None, :, None].float()
+    q, k, v = (x.bfloat16() for x in (q, k, torch.randn(1, T, Hkv, D, generator=g)))
+    idx = _select(torch.randn(1, T, T, generator=g), S)
+    o = torch.empty(1, T, Hq, D, dtype=torch.bfloat16, device="cuda")
+    mb.replay_attention(q.cuda(), k.cuda(), v.cuda(), idx.cuda(), o, 1, T, Hq, Hkv, D, S=S)
+    ref = _attend(q, k, v, idx)
+    d = o.cpu().double() - ref
+    assert d.norm() <= 2.0 ** -7 * ref.norm()
+    assert d.abs().max() <= 2.0 ** -6 * max(1.0, ref.abs().max().item())
+
+
 def test_attention_value_rows_that_are_not_finite():
     """NaN and infinite value rows reach exactly the positions that attend them; their
     group's other positions come out as without them."""
