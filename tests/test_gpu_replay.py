@@ -3,7 +3,7 @@ key selection and replay attention, through the C ABI, against the oracle.
 
 * selection (mot_topS_select): bit-exact key sets on maps with many ties,
   ragged row lengths (rows shorter than S, rows across 256-element chunks),
-  and a 16500-token map (rows longer than the LDS row cache) on sampled
+  and a 16500-token map (rows longer than the registers hold) on sampled
   rows;
 * sparse attention over the selected sets (grouped-query heads, both KV
   layouts, head dims 64 and 128, S = 32 .. 256), sets with padding and
@@ -82,8 +82,8 @@ def test_topS_select_heavy_ties(values, oracle_built):
 
 @pytest.mark.parametrize("T", [2500, 2133])
 def test_topS_select_every_row_of_long_maps(T, oracle_built):
-    """Every row of maps of a few thousand positions (key caches of 10 and
-    8.5 KB; T = 2133 takes the unaligned key fill), against the oracle."""
+    """Every row of maps of a few thousand positions (T = 2133 fetches its keys
+    one by one), against the oracle."""
     from oracle import oracle_topS_select
     print("case select long map T", T, flush=True)
     rng = np.random.default_rng(T)
@@ -101,8 +101,8 @@ def test_topS_select_structured_map(oracle_built):
 
 
 def test_topS_select_long_rows_sampled(oracle_built):
-    """T = 16500 exceeds the LDS row cache: the uncached kernel, on sampled
-    rows (first, last, and around 16384)."""
+    """T = 16500 exceeds what the registers hold: the kernel that reads the row
+    again in every pass, on sampled rows (first, last, and around 16384)."""
     from oracle import oracle_topS_rows
     T, S = 16500, 128
     print("case select long T", T, flush=True)
@@ -127,9 +127,12 @@ ATTN = [  # B, T, H_q, H_kv, D, S, kv_layout
     # LDS swizzle is needed): 12 and 28 chunks
     (1, 240, 6, 2, 64, 96, 0),
     (1, 300, 4, 1, 64, 224, 1),
-    # an odd context: the last position of the two-position kernel is alone
-    (1, 201, 8, 2, 128, 64, 0),
-    (2, 99, 16, 2, 64, 128, 1),       # 8 query heads per KV head: the pair fills all 16 columns
+    (1, 201, 8, 2, 128, 64, 0),       # an odd context
+    (2, 99, 16, 2, 64, 128, 1),       # 8 query heads per KV head
+    # (calls on one or two KV heads this short take the one-position kernel; on
+    # four or more the four-position kernel)
+    (1, 301, 32, 4, 128, 192, 0),     # all 32 columns, the largest S, a lone last position
+    (1, 270, 12, 4, 64, 224, 1),
 ]
 
 
@@ -151,16 +154,18 @@ def test_sparse_attention_parity(case, oracle_built):
     assert worst <= 2 * TOL["bf16"], worst
 
 
+@pytest.mark.parametrize("heads", [(28, 4), (14, 2)], ids=["28x4", "14x2"])
 @pytest.mark.parametrize("order", ["ascending", "shuffled", "duplicates"])
-def test_sparse_pair_union_and_two_pass(order, oracle_built):
-    """The two-position kernel on random sets (neighbouring positions share
-    few keys, so most pairs' unions exceed its 192-key limit and it runs one
-    pass per position), on shuffled sets and on sets with a repeated entry
-    (both taken as listed, one pass per position), for an odd context:
-    every position against the oracle, which attends each listed entry."""
+def test_sparse_unions_and_listed_sets(order, heads, oracle_built):
+    """Random sets (neighbouring positions share few keys, so the four-position
+    kernel's lists run to several hundred), shuffled sets and sets with a
+    repeated entry (which it takes as listed), for an odd context: every
+    position against the oracle, which attends each listed entry.  28 query heads
+    on 4 KV heads take that kernel; 14 on 2, of this length, the one-position
+    kernel."""
     from oracle import oracle_replay_attention
-    B, T, Hq, Hkv, D, S = 1, 401, 14, 2, 128, 128
-    print("case pair kernel", order, flush=True)
+    B, T, (Hq, Hkv), D, S = 1, 401, heads, 128, 128
+    print("case unions", order, heads, flush=True)
     q, k, v = replay_inputs(B, T, Hq, Hkv, D, seed=17)
     rng = np.random.default_rng(17)
     idx = np.full((B, T, S), -1, np.int32)

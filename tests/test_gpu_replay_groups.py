@@ -93,10 +93,15 @@ def test_select_unaligned_base(T, off):
 # KV heads 1, 2, 3, 4 and 8 (one position per workgroup; two groups of two waves,
 # one of them idle or not, and an odd number of groups; one group of four; a wave
 # with two heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V,
-# sets past 128, and lists that are unordered, repeat keys or hold none
+# sets past 128, and lists that are unordered, repeat keys or hold none; then contexts
+# of several times the set, so that every set is full and a group's list runs to
+# hundreds of keys: two groups of two waves per workgroup and one of four, at the
+# largest sets of each head width
 ATTN = [(1, 37, 7, 1, 128, 32, 0), (2, 38, 4, 2, 64, 64, 1), (1, 39, 24, 3, 128, 96, 0), (1, 90, 28, 4, 128, 160, 1),
         (3, 41, 8, 8, 64, 256, 0), (1, 1, 4, 4, 128, 32, 0), (9, 230, 7, 1, 128, 32, 0), (7, 237, 4, 2, 64, 64, 1),
-        (3, 1, 16, 2, 128, 32, 0), (5, 215, 3, 3, 64, 32, 1), (5, 220, 16, 2, 64, 32, 0)]
+        (3, 1, 16, 2, 128, 32, 0), (5, 215, 3, 3, 64, 32, 1), (5, 220, 16, 2, 64, 32, 0),
+        (3, 701, 12, 2, 128, 128, 0), (3, 700, 14, 2, 128, 192, 1), (3, 703, 14, 2, 64, 256, 0),
+        (1, 702, 28, 4, 128, 192, 1), (1, 701, 32, 8, 64, 256, 0)]
 
 
 @pytest.mark.parametrize("case", ATTN, ids=lambda c: "x".join(map(str, c)))
