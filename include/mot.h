@@ -209,10 +209,12 @@ size_t mot_workspace_bytes(const mot_shapes* shapes);
  * short context above all) then cuts its last tiles along the expert-hidden
  * axis over several workgroups each, which leave fp32 partial rows in
  * `scratch` that a second kernel sums.  Same results up to the order of those
- * fp32 sums.  scratch: device, 16-byte aligned, used by this call only (calls
- * that overlap in time need their own), not overlapping a cache or weights;
- * NULL, or fewer bytes than mot_translate_scratch_bytes: exactly
- * mot_translate.  Other paths ignore it.
+ * fp32 sums.  scratch: device memory used by this call only (calls that overlap
+ * in time need their own).  With at least mot_translate_scratch_bytes (and those
+ * not 0) it must be 16-byte aligned (else MOT_ERR_MISALIGNED) and those bytes must
+ * not overlap a cache, the weights, the router or usage (else MOT_ERR_BAD_SHAPE).
+ * With fewer, or NULL, or where mot_translate_scratch_bytes is 0 (as on every other
+ * path), the call is exactly mot_translate and scratch is not looked at.
  */
 mot_status mot_translate_scratch(const void* src_k, const void* src_v, const int32_t* layer_map,
                                  const mot_translator_weights* tw, const mot_router_weights* rw,

@@ -349,13 +349,25 @@ mot_status mot_translate_scratch(const void* src_k, const void* src_v, const int
                 return fail(MOT_ERR_BAD_SHAPE, "workspace overlaps a destination cache");
         }
     }
-    if (scratch) {
-        if (!aligned16(scratch)) return fail(MOT_ERR_MISALIGNED, "scratch %p is not 16-byte aligned", scratch);
-        if (overlaps(scratch, scratch_bytes, dst_k, dst_bytes) ||
-            overlaps(scratch, scratch_bytes, src_k, src_bytes) ||
-            (two && (overlaps(scratch, scratch_bytes, dst_v, dst_bytes) ||
-                     overlaps(scratch, scratch_bytes, src_v, src_bytes))))
-            return fail(MOT_ERR_BAD_SHAPE, "scratch overlaps a cache");
+    // scratch is looked at only where it will be used: by a call that splits tiles
+    FusedSplit split = {nullptr, 0, 0, 1};
+    if (scratch && pl.fused && !pl.routed) {
+        size_t need = 0;
+        split = fused_split_plan(base_problem(s), pl.n_units, &need);
+        split.part = reinterpret_cast<float*>(scratch);
+        if (scratch_bytes < need) split.parts = 1;
+        if (split.parts > 1) {
+            if (!aligned16(scratch)) return fail(MOT_ERR_MISALIGNED, "scratch %p is not 16-byte aligned", scratch);
+            const size_t n = (size_t)s->L_tgt * (two ? 2 : 1) * s->E * es;   // bytes of one element per translator
+            const struct { const void* p; size_t bytes; } args[] = {
+                {dst_k, dst_bytes}, {src_k, src_bytes}, {dst_v, two ? dst_bytes : 0}, {src_v, two ? src_bytes : 0},
+                {tw->w1, n * s->hidden * d_in}, {tw->b1, tw->b1 ? n * s->hidden : 0},
+                {tw->w2, n * d_out * s->hidden}, {tw->b2, tw->b2 ? n * d_out : 0},
+                {rw->w, n * d_in}, {rw->b, rw->b ? n : 0}, {s->usage, s->usage ? usage_bytes : 0}};
+            for (const auto& a : args)
+                if (overlaps(scratch, need, a.p, a.bytes))
+                    return fail(MOT_ERR_BAD_SHAPE, "scratch overlaps a cache, the weights or usage");
+        }
     }
     if (pl.n_units == 0 || n_tok == 0) return MOT_OK;   // nothing to translate
     if (need_min > 0 && !s->workspace) {
@@ -413,10 +425,7 @@ mot_status mot_translate_scratch(const void* src_k, const void* src_v, const int
     } else if (pl.fused) {
         ut.n = pl.n_units;
         memcpy(ut.code, pl.codes, sizeof(uint32_t) * pl.n_units);
-        size_t bytes = 0;
-        if (scratch) p.sp = fused_split_plan(p, pl.n_units, &bytes);
-        if (scratch_bytes < bytes) p.sp.parts = 1;
-        p.sp.part = reinterpret_cast<float*>(scratch);
+        p.sp = split;
         e = launch_bf16_fused(p, ut, stream);
     } else if (!pl.bf16 && f32_split_fits(p)) {
         for (int u0 = 0; e == hipSuccess && u0 < pl.n_units; u0 += group) {

@@ -116,6 +116,46 @@ def test_overlapping_destinations(lib):
     _expect("MOT_ERR_BAD_SHAPE", shapes=_shapes(), ptrs={"dst_k": FAKE})
 
 
+def _scratch_call(shapes, scratch, n_bytes, layer_map=(0, 1), **ptrs):
+    """Status of mot_translate_scratch on the addresses of _call."""
+    p = dict(src_k=FAKE, src_v=FAKE + (1 << 30), w1=FAKE + (2 << 30), b1=None, w2=FAKE + (3 << 30),
+             b2=None, wr=FAKE + (4 << 30), br=None, dst_k=FAKE + (5 << 30), dst_v=FAKE + (6 << 30), usage=None)
+    p.update(ptrs)
+    lm = np.array(layer_map, np.int32)
+    c = shapes.c(usage=p["usage"])
+    tw, rw = mb._TW(p["w1"], p["b1"], p["w2"], p["b2"]), mb._RW(p["wr"], p["br"])
+    rc = mb.load_library().mot_translate_scratch(p["src_k"], p["src_v"], lm.ctypes.data, ctypes.byref(tw),
+                                                 ctypes.byref(rw), p["dst_k"], p["dst_v"], ctypes.byref(c), scratch,
+                                                 n_bytes, None)
+    return mb.STATUS[rc]
+
+
+def test_scratch_checks(lib):
+    """A call that splits checks its scratch: alignment, and overlap with every array;
+    one that does not never looks at it."""
+    sh = _shapes(hidden=512)
+    lm, c = np.array([0, 1], np.int32), sh.c()
+    need = lib.mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+    assert need > 0
+    free = FAKE + (40 << 30)
+    assert _scratch_call(sh, free + 8, need) == "MOT_ERR_MISALIGNED"
+    units = 2 * 2 * 4 * 2                                     # layers, K and V, translators, bytes
+    for name, n in (("src_k", 2 * 8 * 128 * 2), ("src_v", 2 * 8 * 128 * 2), ("dst_k", 2 * 8 * 128 * 2),
+                    ("dst_v", 2 * 8 * 128 * 2), ("w1", units * 512 * 128), ("b1", units * 512), ("w2", units * 128 * 512),
+                    ("b2", units * 128), ("wr", units * 128), ("br", units), ("usage", 2 * 2 * 4 * 4)):
+        # the array's last 16 bytes are scratch's first, or its first scratch's last
+        assert _scratch_call(sh, free, need, **{name: free - n + 16}) == "MOT_ERR_BAD_SHAPE", name
+        assert _scratch_call(sh, free, need, **{name: free + need - 16}) == "MOT_ERR_BAD_SHAPE", name
+    # nothing mapped, on every path: any scratch will do
+    for kw in (dict(hidden=512), dict(hidden=512, top_k=1), dict(hidden=512, algo=mb.ALGO_UNFUSED), dict(dtype=mb.MOT_F32),
+               dict(H_src=4, H_tgt=12)):
+        w = _shapes(**kw)
+        c = w.c()
+        assert lib.mot_translate_scratch_bytes(ctypes.byref(c), np.array([-1, -1], np.int32).ctypes.data) == 0
+        for ptr in (FAKE + 4, FAKE + (5 << 30)):
+            assert _scratch_call(w, ptr, need, layer_map=(-1, -1)) == "MOT_OK"
+
+
 def test_workspace_too_small(lib):
     s = _shapes(algo=mb.ALGO_UNFUSED)
     need = mb.workspace_bytes(s)
