@@ -233,13 +233,47 @@ def translate_raw(src_k, src_v, layer_map, w1, b1, w2, b2, wr, br, dst_k, dst_v,
                              ctypes.byref(c), stream))
 
 
+def translate_scratch_bytes(shapes: Shapes, layer_map: Sequence[int]) -> int:
+    """Bytes of scratch with which ``translate`` splits the last tiles of the
+    fused dense path for a call of these shapes; 0 when it would not."""
+    import numpy as np
+    lm = np.ascontiguousarray(layer_map, dtype=np.int32)
+    if lm.size != shapes.L_tgt:
+        return 0
+    c = shapes.c()
+    return int(load_library().mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data))
+
+
+def _captured_outside_torch(dev) -> bool:
+    """Whether the current stream is being captured into a graph that torch's
+    allocator does not know of: memory taken from it now would be handed out
+    again when the call returns, while the graph goes on writing to it.  (Under
+    torch.cuda.graph allocations come from the graph's own pool.)"""
+    import torch
+    if not torch.cuda.is_current_stream_capturing():
+        return False
+    probe = torch.empty(1, dtype=torch.uint8, device=dev)
+    at = probe.data_ptr()
+    for seg in torch.cuda.memory_snapshot():
+        if seg["address"] <= at < seg["address"] + seg["total_size"]:
+            return tuple(seg.get("segment_pool_id", (0, 0))) == (0, 0)
+    return True
+
+
 def translate(src_k, src_v, layer_map: Sequence[int], w1, b1, w2, b2, wr, br, dst_k, dst_v,
-              shapes: Shapes, workspace=None, usage=None) -> None:
+              shapes: Shapes, workspace=None, usage=None, scratch=None) -> None:
     """Translate on the current torch stream.  Tensors must live on the
     current HIP device, be contiguous and have the dtype named by
     ``shapes.dtype`` (torch.float32 or torch.bfloat16).  ``usage``: optional
     int32 tensor [L_tgt][streams][E] of translator selection counts that the
-    call adds to (the library treats it as uint32)."""
+    call adds to (the library treats it as uint32).
+
+    ``scratch``: memory for the split tiles of the fused dense path
+    (mot_translate_scratch).  None: taken from torch's allocator for this call
+    where the call splits (none under a capture begun outside torch).  A
+    contiguous tensor on the device: used if it holds
+    ``translate_scratch_bytes``, and nothing is allocated.  False: no split, so a
+    token's row has the same bits whatever other tokens the call holds."""
     import numpy as np
     import torch
     want = torch.float32 if shapes.dtype == MOT_F32 else torch.bfloat16
@@ -262,17 +296,26 @@ def translate(src_k, src_v, layer_map: Sequence[int], w1, b1, w2, b2, wr, br, ds
     lib = load_library()
     lm = np.ascontiguousarray(layer_map, dtype=np.int32)
     c = shapes.c(_ptr(workspace), ws_bytes, _ptr(usage))
-    # scratch of the split fused path: allocated for this call on the current
-    # stream, so torch's allocator orders its reuse (under graph capture too);
-    # without room for it the call runs unsplit
-    scratch, n = None, 0
-    if shapes.dtype == MOT_BF16 and lm.size == shapes.L_tgt:
-        n = lib.mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+    n = 0
+    if scratch is None:
+        # allocated for this call on the current stream, so torch's allocator
+        # orders its reuse (under torch.cuda.graph too); without room for it the
+        # call runs unsplit
+        if shapes.dtype == MOT_BF16 and lm.size == shapes.L_tgt:
+            n = lib.mot_translate_scratch_bytes(ctypes.byref(c), lm.ctypes.data)
+        if n and _captured_outside_torch(dev):
+            n = 0
         if n:
             try:
                 scratch = torch.empty(n, dtype=torch.uint8, device=dev)
             except torch.cuda.OutOfMemoryError:
                 n = 0
+    elif scratch is False:
+        scratch = None
+    else:
+        if scratch.device != dev or not scratch.is_contiguous():
+            raise MotError(2, "scratch must be a contiguous tensor on %s" % dev)
+        n = scratch.numel() * scratch.element_size()
     tw = _TW(_ptr(w1), _ptr(b1), _ptr(w2), _ptr(b2))
     rw = _RW(_ptr(wr), _ptr(br))
     _check(lib.mot_translate_scratch(_ptr(src_k), _ptr(src_v), lm.ctypes.data if lm.size else None,

@@ -114,3 +114,106 @@ def test_split_under_graph_capture():
         assert all(torch.equal(a, b) for a, b in zip(*out))
         call(out[0])
         torch.cuda.synchronize()
+
+
+def _small(T, **kw):
+    """A headline-like call of few layers, its arguments on the GPU and its map."""
+    w = small_variant(WORKLOADS[3], L_src=2, L_tgt=2, B=1, T=T, **kw)
+    inp = generate(w)
+    d = {n: to_dev(getattr(inp, n), w.dtype) for n in ("src_k", "src_v", "w1", "b1", "w2", "b2", "wr", "br")}
+    return w, d
+
+
+def _translate(w, d, **kw):
+    import torch
+    out = [torch.full(dst_shape(w), -3.75, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    mb.translate(d["src_k"], d["src_v"], [0, 1], d["w1"], d["b1"], d["w2"], d["b2"], d["wr"], d["br"], *out,
+                 mb.Shapes.from_workload(w), **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.gpu
+def test_scratch_argument():
+    """The caller's scratch gives the bits of the allocated one and nothing is allocated;
+    one byte too few, False and mot_translate give those of the unsplit call."""
+    import torch
+    w, d = _small(37)
+    sh = mb.Shapes.from_workload(w)
+    n = mb.translate_scratch_bytes(sh, [0, 1])
+    assert n > 0 and n == _scratch_bytes(w, [0, 1])
+    own, whole = _translate(w, d), _translate(w, d, scratch=False)
+    buf = torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda")
+    assert not all(torch.equal(a, b) for a, b in zip(own, whole))        # (they differ in a last bit somewhere)
+    out = [torch.empty_like(x) for x in own]
+    args = (d["src_k"], d["src_v"], [0, 1], d["w1"], d["b1"], d["w2"], d["b2"], d["wr"], d["br"], *out, sh)
+    for kw, want in ((dict(scratch=buf), own), (dict(scratch=buf[:n - 1]), whole), (dict(scratch=buf[1:n]), whole),
+                     (dict(scratch=False), whole)):
+        for x in out:
+            x.fill_(-3.75)
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        mb.translate(*args, **kw)
+        torch.cuda.synchronize()
+        assert torch.cuda.max_memory_allocated() == before
+        assert all(torch.equal(a, b) for a, b in zip(out, want)), kw.keys()
+    mb.translate_raw(*args)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, whole))
+    with pytest.raises(mb.MotError) as e:
+        mb.translate(*args, scratch=torch.empty(n + 16, dtype=torch.uint8, device="cuda")[8:])
+    assert e.value.name == "MOT_ERR_MISALIGNED"
+
+
+@pytest.mark.gpu
+def test_rows_of_a_sub_batch():
+    """Without a split a token's rows keep their bits whatever else the call holds; with
+    one they may move to the neighbouring bf16 value."""
+    import torch
+    w, d = _small(600)
+    part = w.with_(T=512)
+    sub = dict(d, src_k=d["src_k"][:, :, :512].contiguous(), src_v=d["src_v"][:, :, :512].contiguous())
+    assert _scratch_bytes(w, [0, 1]) != _scratch_bytes(part, [0, 1])
+    for a, b in zip(_translate(w, d, scratch=False), _translate(part, sub, scratch=False)):
+        assert torch.equal(a[:, :, :512], b)
+    for a, b in zip(_translate(w, d), _translate(part, sub)):
+        a, b = a[:, :, :512].double(), b.double()
+        # neighbours, or sums of cancelling terms apart by their fp32 rounding
+        assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.square().mean().sqrt()).all()
+
+
+@pytest.mark.gpu
+def test_capture_begun_outside_torch():
+    """A graph captured through the HIP runtime: the call takes no memory that torch's
+    allocator would hand out again, and replays give the unsplit result."""
+    import torch
+    path, = mb._hip_runtimes()
+    hip = ctypes.CDLL(path)
+    w, d = _small(37)
+    want = _translate(w, d, scratch=False)
+    out = [torch.zeros_like(x) for x in want]
+    args = (d["src_k"], d["src_v"], [0, 1], d["w1"], d["b1"], d["w2"], d["b2"], d["wr"], d["br"], *out,
+            mb.Shapes.from_workload(w))
+    torch.empty(1, dtype=torch.uint8, device="cuda")          # (its block is kept by the allocator)
+    stream = torch.cuda.Stream()
+    st, graph, ex = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    with torch.cuda.stream(stream):
+        assert hip.hipStreamBeginCapture(st, 2) == 0           # relaxed mode
+        try:
+            mb.translate(*args)
+        finally:
+            rc = hip.hipStreamEndCapture(st, ctypes.byref(graph))
+    assert rc == 0 and torch.cuda.max_memory_allocated() - before < 4096
+    assert hip.hipGraphInstantiate(ctypes.byref(ex), graph, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        for x in out:
+            x.zero_()
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(ex, st) == 0
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+        _translate(w, d)
+    assert hip.hipGraphExecDestroy(ex) == 0 and hip.hipGraphDestroy(graph) == 0
