@@ -209,7 +209,9 @@ size_t mot_workspace_bytes(const mot_shapes* shapes);
  * short context above all) then cuts its last tiles along the expert-hidden
  * axis over several workgroups each, which leave fp32 partial rows in
  * `scratch` that a second kernel sums.  Same results up to the order of those
- * fp32 sums.  scratch: device memory used by this call only (calls that overlap
+ * fp32 sums: which tiles are cut depends on the whole call, so a token's row may
+ * differ in its last bit from its row in a call with other tokens (mot_translate's
+ * fused path gives it the same bits in both).  scratch: device memory used by this call only (calls that overlap
  * in time need their own).  With at least mot_translate_scratch_bytes (and those
  * not 0) it must be 16-byte aligned (else MOT_ERR_MISALIGNED) and those bytes must
  * not overlap a cache, the weights, the router or usage (else MOT_ERR_BAD_SHAPE).

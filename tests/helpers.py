@@ -27,9 +27,10 @@ def dst_shape(w):
 
 
 def run_gpu(w, inp: Inputs, layer_map, algo=mb.ALGO_AUTO, act=mb.ACT_GELU, with_bias=True,
-            dev=None):
+            dev=None, **kw):
     """Translate on the GPU through the C ABI; returns (dst_k, dst_v) as
-    float64 numpy arrays in the dst layout (unmapped layers hold SENTINEL)."""
+    float64 numpy arrays in the dst layout (unmapped layers hold SENTINEL);
+    kw: further arguments of translate."""
     import torch
     d = dev or {}
     if not d:
@@ -41,7 +42,7 @@ def run_gpu(w, inp: Inputs, layer_map, algo=mb.ALGO_AUTO, act=mb.ACT_GELU, with_
     shapes = mb.Shapes.from_workload(w, algo=algo, act=act)
     mb.translate(d["src_k"], d["src_v"], layer_map, d["w1"], d["b1"] if with_bias else None,
                  d["w2"], d["b2"] if with_bias else None, d["wr"], d["br"] if with_bias else None,
-                 dk, dv, shapes)
+                 dk, dv, shapes, **kw)
     torch.cuda.synchronize()
     return dk.float().cpu().numpy().astype(np.float64), dv.float().cpu().numpy().astype(np.float64)
 
