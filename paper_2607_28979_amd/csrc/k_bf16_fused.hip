@@ -40,13 +40,13 @@ bool fused_supported(const Problem& p) {
 
 namespace {
 
-// Tile rows and LDS bytes of the instantiation for (d_in, d_out)
+// Tile rows of the instantiation for (d_in, d_out), and workgroups a CU holds
 struct Tile {
-    int rows, lds;
+    int rows, wgs;
 };
 Tile fused_tile(const Problem& p) {
     switch (p.d_in * 1000 + p.d_out) {
-#define MOT_TILE(a, b) case a * 1000 + b: return {Cfg<a, b>::BM, Cfg<a, b>::TOTAL * 16};
+#define MOT_TILE(a, b) case a * 1000 + b: return {Cfg<a, b>::BM, Cfg<a, b>::WGS};
         MOT_TILE(128, 128) MOT_TILE(128, 256) MOT_TILE(128, 512)
         MOT_TILE(256, 128) MOT_TILE(256, 256) MOT_TILE(256, 512)
         MOT_TILE(512, 128) MOT_TILE(512, 256) MOT_TILE(512, 512)
@@ -63,36 +63,47 @@ int fused_tile_rows(const Problem& p) { return fused_tile(p).rows; }
 // CUs idle for a whole walk of E*hidden (a call of one tile per unit keeps 56
 // of 256 busy).  The tiles past the last full round are then cut along the
 // walk into `parts` workgroups each.  The choice minimises the modelled time
-// of those tiles, in chunk iterations (about 1.25 us each, in every
-// instantiation): rounds * (chunks per part + a fixed cost of 8 for the
-// router, pipeline fill and drain and stores, 6 more for a partial tile's
-// fp32 stores) plus the combine (its launch, and the partial tiles written
-// and read at 4 TB/s).  A split must save 2 % of the call.  Measured, 1.5B ->
-// 7B with 37 tokens (56 tiles, 4 parts): 669 -> 271 us, now the time to read
-// the 1.4 GB of weights (5.2 TB/s); 7B -> 7B with 1501 tokens (896 tiles, the
-// last 128 in 2 parts): 3662 -> 3282 us.
+// of those tiles, in chunk iterations: rounds * (chunks per part + a fixed cost
+// of 8 for the router, pipeline fill and drain and stores, 6 more for a partial
+// tile's fp32 stores) plus the combine (its launch, and the partial tiles written
+// and read at 4 TB/s, in iterations of 1.25 us: they take 0.8 us, 256 -> 128, to 1.8,
+// 512 -> 512).  Where a CU holds two workgroups, a round of at most one per CU runs its
+// chunks in 0.7 of the time (128 -> 128: 0.58 us for one, 1.09 for two).  A split
+// must save 2 % of the call.
+//
+// Measured, 1.5B -> 7B with 37 tokens (56 tiles, 4 parts): 669 -> 271 us, now
+// the time to read the 1.4 GB of weights (5.2 TB/s); 7B -> 7B with 1501 tokens (896
+// tiles, the last 128 in 2 parts): 3637 -> 3349 us.  Against every count of parts up
+// to 16 for 117 calls (11 shapes, 1 to 3000 tokens), the rule's was 0.4 % above the
+// best on average and never above the unsplit call.
 FusedSplit fused_split_plan(const Problem& p, int n_units, size_t* bytes) {
     constexpr int kCUs = 256, kMaxParts = 16;
     constexpr size_t kMaxBytes = size_t(256) << 20;
-    constexpr double kChunkUs = 1.25, kFixed = 8, kPartFixed = 6, kCombineUs = 4, kBytesPerUs = 4e6;
+    constexpr double kChunkUs = 1.25, kFixed = 8, kPartFixed = 6, kCombineUs = 4, kBytesPerUs = 4e6,
+                     kAlone = 0.7;
     FusedSplit sp = {nullptr, 0, 0, 1};
     *bytes = 0;
     const Tile tl = fused_tile(p);
     if (tl.rows == 0 || n_units == 0 || p.n_tok == 0) return sp;
     const int64_t tiles = (int64_t)((p.n_tok + tl.rows - 1) / tl.rows) * n_units;
-    const int slots = kCUs * (160 * 1024 / tl.lds);
+    const int slots = kCUs * tl.wgs;
     const int tail = (int)(tiles % slots), nch = p.E * p.hidden / 32;
     if (tail == 0 || tiles > (int64_t)1 << 30) return sp;
-    const double whole = (double)(tiles / slots) * (nch + kFixed), unsplit = nch + kFixed;
+    // n workgroups of c chunks and a fixed cost f, in rounds
+    auto rounds = [&](int64_t n, double c, double f) {
+        const int64_t rest = n % slots;
+        const double alone = tl.wgs > 1 && rest <= kCUs ? kAlone : 1;
+        return (double)(n / slots) * (c + f) + (rest ? c * alone + f : 0);
+    };
+    const double whole = (double)(tiles / slots) * (nch + kFixed), unsplit = rounds(tail, nch, kFixed);
     const size_t tile_bytes = (size_t)tl.rows * p.d_out * sizeof(float);
     const double rows = (double)(p.n_tok < tl.rows ? p.n_tok : tl.rows);
     double best = unsplit - 0.02 * (whole + unsplit);
     for (int parts = 2; parts <= kMaxParts && parts <= nch / 2; ++parts) {
         const int64_t wgs = (int64_t)tail * parts;
         if (wgs * tile_bytes > kMaxBytes) break;
-        const double rounds = (double)((wgs + slots - 1) / slots);
         const double combine = kCombineUs + 2.0 * wgs * rows * p.d_out * sizeof(float) / kBytesPerUs;
-        const double t = rounds * ((double)nch / parts + kFixed + kPartFixed) + combine / kChunkUs;
+        const double t = rounds(wgs, (double)nch / parts, kFixed + kPartFixed) + combine / kChunkUs;
         if (t < best) {
             best = t;
             sp.parts = parts;

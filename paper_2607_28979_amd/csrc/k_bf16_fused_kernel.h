@@ -117,6 +117,11 @@ struct Cfg {
     static constexpr int OFF_G = OFF_H + 2 * H_CH;
     static constexpr int OFF_X = OFF_G + GS / 4;
     static constexpr int TOTAL = OFF_X + 2 * X_CH;
+    // workgroups a CU holds at once: two of 128 -> 128 (64 KB of LDS each, 107 VGPRs:
+    // four waves per SIMD), one of the others.  256 -> 128 has the LDS for two, but at
+    // 136 VGPRs a SIMD holds three waves, and two workgroups are four.
+    static constexpr int WGS = D_IN == 128 && D_OUT == 128 ? 2 : 1;
+    static_assert(WGS * TOTAL * 16 <= 160 * 1024, "LDS of the workgroups of a CU");
     static_assert(NOFF == 0 || NOFF == 4 || NOFF == 8, "offloaded GELU elements");
     static_assert(TOTAL * 16 <= 160 * 1024, "LDS");
     static_assert(W1_CH % 256 == 0 && W2_CH % 256 == 0 && NBW >= 1, "tile shape");

@@ -34,6 +34,28 @@ def test_scratch_rule():
     assert lib.mot_translate_scratch_bytes(ctypes.byref(c), None) == 0
 
 
+@pytest.mark.parametrize("d_in,d_out,slots,rows", [(128, 128, 512, 128), (256, 128, 256, 128), (128, 256, 256, 128),
+                                                   (512, 128, 256, 128), (512, 512, 256, 96)])
+def test_tail_past_full_rounds(d_in, d_out, slots, rows):
+    """Only the tiles past the last round that the chip holds are split: one workgroup
+    per CU, two of 128 -> 128 (256 -> 128 has the LDS for two but not the registers)."""
+    units, ntx = 20, slots // 20 + 2
+    tail = units * ntx % slots
+    sh = mb.Shapes(10, 10, 1, ntx * rows, 1, d_in, 1, d_out, 4, 4096)
+    n = mb.translate_scratch_bytes(sh, range(10))
+    parts, rest = divmod(n, tail * rows * d_out * 4)
+    assert 0 < tail < 64 and 2 <= parts <= 16 and rest == 0
+
+
+def test_no_split_where_one_workgroup_per_cu_is_faster():
+    """128 -> 128, 24 layers, E * hidden 2048 and 240 tiles: unsplit 50.5 us, in two
+    parts 57.3 (each CU then runs two workgroups)."""
+    w = WORKLOADS[1].with_(B=1)
+    assert (w.d_in, w.d_out, w.E * w.hidden, w.units()) == (128, 128, 2048, 48)
+    for T, split in ((37, True), (200, True), (391, False), (600, False), (1501, True)):
+        assert (_scratch_bytes(w.with_(T=T), range(24)) > 0) == split, T
+
+
 # (workload, variant): one token, a partial tile of each row count (128 and 96),
 # several parts that do not divide the walk, full tiles ahead of the split ones
 # (one workgroup per CU, and two), usage, an unmapped layer, BHTD
