@@ -216,7 +216,8 @@ def main():
     # the library's rule for the fp32 matrix-core kernels (else router + vector-ALU GEMMs)
     f32_split = w.dtype == "f32" and w.hidden % 64 == 0 and w.d_in % 16 == 0 and w.d_out % 4 == 0
     achieved_tflops = flops / (avg_call_ms / 1e3) / 1e12
-    peak = PEAK_TFLOPS[w.dtype]
+    # the split kernels form an fp32 product from eight bf16 ones
+    peak = PEAK_TFLOPS["bf16"] / 8 if f32_split else PEAK_TFLOPS[w.dtype]
     roofline = {
         "bound": "mfma",
         "kernel": ("k_bf16_fused" if fused else "k_f32_split_gemm1 + k_f32_split_gemm2" if f32_split else
@@ -225,7 +226,7 @@ def main():
                       " + combine" if w.top_k > 1 else "") if routed
                    else "mot_translate (router + gemm1 + gemm2)"),
         "achieved": round(achieved_tflops, 2),
-        "peak": peak,
+        "peak": round(peak, 1),
         "unit": "TFLOP/s",
         "frac": round(achieved_tflops / peak, 4),
         "traffic": (None if routed or args.top_k else
@@ -416,6 +417,15 @@ def cpu_baseline_moth(w, inp, lm, proj, rows):
             "seconds": round(dt, 2)}
 
 
+def takes_group_kernel(w) -> bool:
+    """The library's rule for the four-position sparse kernel, K and V in BTHD: at
+    most 8 query heads per KV head, a batch row of K under 2 GiB, and not a small call
+    on one or two KV heads."""
+    row = w.H_kv * w.D
+    small = w.H_kv <= 2 and w.B * w.T * row <= 128 * 1024
+    return 4 * (w.H_q // w.H_kv) <= 32 and (w.T + 64) * row * 2 < 2 ** 31 and not small
+
+
 def group_gathered_rows(idx, T: int) -> float:
     """Key rows the four-position sparse kernel gathers per KV head for one
     launch: for each group of positions u .. u+3 of every batch row, the size of
@@ -508,7 +518,7 @@ def bench_replay(args):
     # selected K and V rows it gathers per (query, KV head) are reported beside
     sp_gather_sets = 2.0 * 2 * w.D * w.H_kv * w.B * sum(min(u + 1, w.S) for u in range(w.T))
     sp_gather = sp_gather_sets
-    group = 4 * (w.H_q // w.H_kv) <= 32   # the library's rule for that kernel
+    group = takes_group_kernel(w)
     if group:
         # the four-position kernel gathers the union of a group's sets once:
         # count the rows on this run's own sets, averaged over the sparse layers
