@@ -73,8 +73,8 @@ int fused_tile_rows(const Problem& p) { return fused_tile(p).rows; }
 //
 // Measured, 1.5B -> 7B with 37 tokens (56 tiles, 4 parts): 669 -> 271 us, now
 // the time to read the 1.4 GB of weights (5.2 TB/s); 7B -> 7B with 1501 tokens (896
-// tiles, the last 128 in 2 parts): 3637 -> 3349 us.  Against every count of parts up
-// to 16 for 117 calls (11 shapes, 1 to 3000 tokens), the rule's was 0.4 % above the
+// tiles, the last 128 in 2 parts): 3558 -> 3233 us.  Against every count of parts up
+// to 16 for 124 calls (11 shapes, 1 to 3000 tokens), the rule's was 0.4 % above the
 // best on average and never above the unsplit call.
 FusedSplit fused_split_plan(const Problem& p, int n_units, size_t* bytes) {
     constexpr int kCUs = 256, kMaxParts = 16;

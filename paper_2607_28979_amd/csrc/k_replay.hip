@@ -5,22 +5,24 @@
 //   with the largest head-averaged source attention A[b][u][v] (ties to the
 //   lower position), in ascending position order, padded with -1.  Radix
 //   select over order-preserving 32-bit keys: a lower bound from the threads'
-//   largest keys, then a 1024-bin histogram of the top 10 bits above it finds the bin holding the S-th largest key; that bin's keys
-//   (a few dozen on attention rows) are ranked against each other for the
-//   exact key, or, past 256 of them, 8-bit radix passes over the lower bits
-//   finish the search; then one ordered pass keeps every larger key and the
-//   lowest-positioned equal ones.
+//   largest keys, then a 1024-bin histogram of the top 10 bits above it finds
+//   the bin holding the S-th largest key; that bin's keys (a few dozen on
+//   attention rows) are ranked against each other for the exact key, or, past
+//   256 of them, 8-bit radix passes over the lower bits finish the search; then
+//   one ordered pass keeps every larger key and the lowest-positioned equal ones.
 // * k_sparse_attn_group: attention of every query head over the key sets
 //   (grouped-query: query head h reads KV head h / G), four positions and one
 //   KV head per wave over the union of the positions' sets, for G <= 8.
 // * k_sparse_attn: the same for one position (more than 8 query heads per KV
-//   head, K of 2 GiB and more per batch row, small calls on few KV heads).  Per KV head the
-//   workgroup computes scores^T = K_sel . Q^T on v_mfma_f32_16x16x32_bf16 with
-//   the gathered key rows loaded straight into A operands, a softmax over the
-//   set, and O^T = V_sel^T . P^T with V_sel staged transposed in LDS.
-// * k_causal_attn: the full causal attention of the bottom layers, tiled
-//   (tiles of 128 query positions of one head, 64-key chunks of K and V^T loaded straight into LDS one chunk
-//   ahead, online softmax, v_mfma_f32_32x32x16_bf16).
+//   head, K of 2 GiB and more per batch row, small calls on few KV heads).  Per
+//   KV head the workgroup computes scores^T = K_sel . Q^T on
+//   v_mfma_f32_16x16x32_bf16 with the gathered key rows loaded straight into A
+//   operands, a softmax over the set, and O^T = V_sel^T . P^T with V_sel staged
+//   transposed in LDS.
+// * k_causal_attn: the full causal attention of the bottom layers, tiled (tiles
+//   of 128 query positions of one head, 64-key chunks of K and V^T loaded
+//   straight into LDS one chunk ahead, online softmax,
+//   v_mfma_f32_32x32x16_bf16).
 // Scores, softmax and accumulation are fp32; Q, K, V, O are bf16.
 #include "mot_device.h"
 #include "mot_internal.h"
@@ -142,9 +144,9 @@ struct RowKeys {
     }
 };
 
-// Bound: vector instructions per key.  8192 rows of a causal map, sets of 128: 120
+// Bound: vector instructions per key.  8192 rows of a causal map, sets of 128: 119
 // us with the row's keys in LDS (4 workgroups per CU, every key counted by an LDS
-// atomic), 60 us with them in registers and one key in ten counted.
+// atomic), 55 us with them in registers and one key in ten counted.
 //
 // grid (T, B), 256 threads; dynamic LDS: per-chunk counts s_gt, s_eq
 // (T / (64 Q) + 4 each)
@@ -674,7 +676,7 @@ __global__ __launch_bounds__(256) void k_sparse_attn(ReplayProblem p) {
 // Bound: latency (waves wait half their time; 2 per SIMD is what the tiles and
 // accumulators leave room for).  28 query heads on 4 KV heads of 128, 8192
 // positions, sets of 128: 252 us with two positions per workgroup and V transposed
-// by 4-byte LDS stores, 88 us now (0.67 GB gathered instead of 1.2).
+// by 4-byte LDS stores, 97 us now (0.67 GB gathered instead of 1.2).
 //
 // grid xcd_grid(ceil(B * ceil(T / 4) / (4 / WPG))), 256 threads
 constexpr int kPos = 4;   // positions per group
