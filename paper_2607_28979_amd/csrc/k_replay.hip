@@ -144,9 +144,11 @@ struct RowKeys {
     }
 };
 
-// Bound: vector instructions per key.  8192 rows of a causal map, sets of 128: 119
+// Bound: latency of its passes and vector instructions (waves wait 57 % of their
+// cycles, the vector ALUs are 39 % busy).  8192 rows of a causal map, sets of 128: 119
 // us with the row's keys in LDS (4 workgroups per CU, every key counted by an LDS
-// atomic), 55 us with them in registers and one key in ten counted.
+// atomic), 55 us with them in registers and one key in ten counted (6 waves per SIMD
+// spill 8 registers: 55 MB of writes beside the 4 MB of sets).
 //
 // grid (T, B), 256 threads; dynamic LDS: per-chunk counts s_gt, s_eq
 // (T / (64 Q) + 4 each)

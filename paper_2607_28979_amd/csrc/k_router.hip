@@ -137,10 +137,13 @@ __global__ __launch_bounds__(256) void k_router(Problem p, UnitTab ut) {
 // source loads in flight.  Every lane gets its token's E logits by shuffles;
 // lanes 0..15 own the tokens.
 //
-// Bound: the source rows' bytes.  With the form above on packed bf16 dot products
-// (E LDS reads and 4 E dot products per 8 values and token) a Top-1 call over 8
-// translators of 256-wide rows (4096 tokens, 56 units) took 989 us, with this one
-// 930; a dense call on 2048-wide rows (2048 tokens, 4 translators) 2524 and 2470.
+// Bound: the source rows' bytes where rows are wide (2048 values, 16384 tokens, 56
+// units: 3.8 GB in 637 us, 6.0 TB/s); at 256 values (4096 tokens, 56 units: 44 us,
+// 2.7 TB/s) the shuffles, softmax and Top-K of a token as much (vector ALUs 45 %
+// busy).  With the form above on packed bf16 dot products (E LDS reads and 4 E dot
+// products per 8 values and token) a Top-1 call over 8 translators of 256-wide rows
+// (4096 tokens, 56 units) took 989 us, with this one 930; a dense call on 2048-wide
+// rows (2048 tokens, 4 translators) 2524 and 2470.
 //
 // grid: x = groups of 64 tokens, strided; y = unit; 256 threads
 constexpr int kStepsAhead = 8;
