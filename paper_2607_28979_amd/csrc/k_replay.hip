@@ -58,42 +58,46 @@ constexpr int kSelBits = 10, kSelBins = 1 << kSelBits;   // first radix digit
 constexpr int kSelCand = 256;                              // boundary-bin keys ranked directly
 static_assert(kSelBins == 4 * 256, "four first-digit bins per thread");
 
-// Where a selection's keys come from.  RegKeys: the row in registers, NV 16-byte
-// pieces per thread (piece i of thread t: positions 1024 i + 4 t .. +3), for T <=
-// 1024 NV.  RowKeys: read from the row again in every pass, one per thread and
-// 256 positions (longer rows).
+// Where a selection's keys come from.  RegKeys: the row in registers, NV pieces of Q
+// values per thread (piece i of thread t: positions 256 Q i + Q t .. + Q - 1), for T
+// <= 256 Q NV.  RowKeys: read from the row again in every pass, one per thread and
+// 256 positions (longer rows).  BOUND: length from which a row is searched for a
+// lower bound before its keys are counted (0: never).
 //
 // for_each<EXACT>(f): f(key) for every position < n of this thread, and, unless
 // EXACT, f(0) for others (0 is the least key); chunks(f): f(chunk,
 // this lane's Q keys, their first position, n) for each chunk of 64 Q positions of
 // this wave, by all its lanes (positions >= n among them).
-template <int NV>
+template <int NV, int Q_ = 4>
 struct RegKeys {
-    static constexpr int Q = 4;
+    static constexpr int Q = Q_, P = 256 * Q;   // positions of a piece of the threads
+    // shorter rows pay more for the extra pass than its atomics cost (a map of 2048
+    // positions, sets of 128: 13.1 us with it from 1024 on, 12.3 without)
+    static constexpr int BOUND = P * NV > 3072 ? 3072 : 0;
     // waves per SIMD the registers are limited to (NV = 8: 6 measured best of 4, 6, 8)
-    static constexpr int WAVES = NV <= 8 ? 6 : 4;
-    u32x4 k[NV];
+    static constexpr int WAVES = NV <= 4 ? 8 : NV <= 8 ? 6 : 4;
+    uint32_t k[NV][Q];
     int n;
     __device__ __forceinline__ void load(const float* row, int T, int n_) {
         n = n_;
         // a row on a 16-byte boundary with T % 4 == 0 (uniform): a piece may end past
         // u, still inside the row; the rest is never used
-        const bool whole = (T & 3) == 0 && (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+        const bool whole = Q == 4 && (T & 3) == 0 && (reinterpret_cast<uintptr_t>(row) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int v = 1024 * i + 4 * threadIdx.x;
+            const int v = P * i + Q * threadIdx.x;
             f32x4 a = {0.f, 0.f, 0.f, 0.f};
             if (v < n) {
                 if (whole) {
                     a = *reinterpret_cast<const f32x4*>(row + v);
                 } else {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
+                    for (int c = 0; c < Q; ++c)
                         if (v + c < n) a[c] = row[v + c];
                 }
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) k[i][c] = v + c < n ? order_key(a[c]) : 0u;
+            for (int c = 0; c < Q; ++c) k[i][c] = v + c < n ? order_key(a[c]) : 0u;
         }
     }
     // n as a new value in each pass: the comparisons with it are made again
@@ -108,22 +112,23 @@ struct RegKeys {
         const int m = bound();
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            if (1024 * i < m)   // uniform
+            if (P * i < m)   // uniform
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (!EXACT || 1024 * i + 4 * (int)threadIdx.x + c < m) f(k[i][c]);
+                for (int c = 0; c < Q; ++c)
+                    if (!EXACT || P * i + Q * (int)threadIdx.x + c < m) f(k[i][c]);
     }
     template <class F>
     __device__ __forceinline__ void chunks(F f) const {
         const int m = bound();
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            if (1024 * i < m) f(4 * i + (threadIdx.x >> 6), k[i], 1024 * i + 4 * (int)threadIdx.x, m);
+            if (P * i < m) f(4 * i + (threadIdx.x >> 6), k[i], P * i + Q * (int)threadIdx.x, m);
     }
 };
 
 struct RowKeys {
     static constexpr int Q = 1, WAVES = 8;
+    static constexpr int BOUND = 0;   // T = 17000, sets of 128: 753 us with it, 633 without
     const float* row;
     int n;
     __device__ __forceinline__ void load(const float* r, int, int n_) {
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(256, Keys::WAVES) void k_topS_select(const float* A
     extern __shared__ int s_gt[];
     constexpr int Q = Keys::Q;
     __shared__ uint32_t hist[kSelBins];
-    __shared__ uint32_t hist_max[kSelBins];
+    __shared__ uint32_t hist_max[Keys::BOUND > 0 ? kSelBins : 1];
     __shared__ uint32_t s_cand[kSelCand];
     __shared__ uint32_t s_sel[3], s_wsum[4];
     __shared__ int s_cnt;
@@ -178,7 +183,12 @@ __global__ __launch_bounds__(256, Keys::WAVES) void k_topS_select(const float* A
     constexpr int sh1 = 32 - kSelBits;
     if (tid < 64) s_cnt = 0;
 #pragma unroll
-    for (int i = 0; i < kSelBins / 256; ++i) hist[tid + 256 * i] = hist_max[tid + 256 * i] = 0;
+    for (int i = 0; i < kSelBins / 256; ++i) hist[tid + 256 * i] = 0;
+    static_assert(Keys::BOUND == 0 || Keys::BOUND >= 256 * Q, "every thread holds a key");
+    const bool bound = Keys::BOUND > 0 && S <= 256 && n >= Keys::BOUND;   // uniform
+    if (bound)
+#pragma unroll
+        for (int i = 0; i < kSelBins / 256; ++i) hist_max[tid + 256 * i] = 0;
     __syncthreads();
     // the bin of h holding the S-th largest key -> s_sel: thread t holds bins
     // 4t .. 4t+3, suffix sums over the threads (within each wave by shuffles, then
@@ -215,12 +225,12 @@ __global__ __launch_bounds__(256, Keys::WAVES) void k_topS_select(const float* A
         }
         __syncthreads();
     };
-    // A lower bound first: when every thread holds a key and S <= 256, S of the
+    // A lower bound first: every thread holds a key and S <= 256, so S of the
     // threads' largest keys reach the bin of the S-th largest of those, so the
     // row's S-th largest key does too, and the keys below that bin (nine in ten
     // of a long row) need no atomic
     uint32_t d0 = 0;
-    if (S <= 256 && n >= 256 * Q) {   // uniform
+    if (bound) {
         uint32_t mx = 0;
         keys.template for_each<false>([&](uint32_t k) { mx = k > mx ? k : mx; });
         atomicAdd(&hist_max[mx >> sh1], 1u);
@@ -1239,7 +1249,11 @@ hipError_t launch_topS_select(const float* A, int32_t* idx, int B, int T, int S,
     const dim3 grid(T, B);
     const auto lds = [&](int q) { return (size_t)2 * (T / (64 * q) + 4) * sizeof(int); };
     // the row in registers up to 16 pieces per thread
-    if (T <= 8192) hipLaunchKernelGGL(k_topS_select<RegKeys<8>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    if (T <= 256) hipLaunchKernelGGL((k_topS_select<RegKeys<1, 1>>), grid, dim3(256), lds(1), stream, A, idx, T, S);
+    else if (T <= 1024) hipLaunchKernelGGL(k_topS_select<RegKeys<1>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    else if (T <= 2048) hipLaunchKernelGGL(k_topS_select<RegKeys<2>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    else if (T <= 4096) hipLaunchKernelGGL(k_topS_select<RegKeys<4>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
+    else if (T <= 8192) hipLaunchKernelGGL(k_topS_select<RegKeys<8>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
     else if (T <= 16384) hipLaunchKernelGGL(k_topS_select<RegKeys<16>>, grid, dim3(256), lds(4), stream, A, idx, T, S);
     else hipLaunchKernelGGL(k_topS_select<RowKeys>, grid, dim3(256), lds(1), stream, A, idx, T, S);
     return hipGetLastError();

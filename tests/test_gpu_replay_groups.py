@@ -42,9 +42,24 @@ def _attend(q, k, v, idx):
 # below 256 (the lower bound), S = 1, and rows longer than the registers hold
 @pytest.mark.parametrize("T,S", [(1030, 32), (1029, 300), (2051, 256), (1100, 1), (8196, 64), (16388, 32)])
 def test_select_edges(T, S):
+    _check_select(T, S, {S, S + 1, 1023, 1024, 1025, T // 2, T - 2, T - 1})
+
+
+# a map at the last length of each form (one piece of one or of four values per thread,
+# two, four, eight and sixteen pieces) and at the first of the next, with rows on both
+# sides of the length from which a lower bound is looked for (3072), S to 256 and past it
+# (rows much longer than S: at a boundary of 0 the zeros' signs would count)
+@pytest.mark.parametrize("T,S", [(2, 1), (255, 16), (256, 255), (257, 16), (1024, 90), (1025, 300), (2048, 256), (2049, 64),
+                                 (3080, 256), (3080, 257), (4096, 32), (4097, 128), (8192, 256), (8193, 1), (16384, 64),
+                                 (16385, 256)])
+def test_select_forms(T, S):
+    _check_select(T, S, {S, T // 3, 2047, 3070, 3071, 3072, T - 2, T - 1})
+
+
+def _check_select(T, S, us):
     print("case", T, S, flush=True)
     g = torch.Generator().manual_seed(T)
-    rows = sorted({S, S + 1, 1023, 1024, 1025, T // 2, T - 2, T - 1} & set(range(T)))
+    rows = sorted(us & set(range(T)))
     A = torch.zeros(1, T, T, device="cuda")
     want = {}
     for i, u in enumerate(rows):
