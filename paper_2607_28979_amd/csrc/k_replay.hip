@@ -1040,17 +1040,10 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // tile's last position.  Workgroups go to the 8 XCDs round-robin, and every XCD
 // takes a contiguous share of the heads (the heads of a KV group meet in one L2).
 //
-// causal_paired: a workgroup runs a short and a long tile, so that all do the same
-// work.  Grid xcd_grid(pairs * H_q * B), pairs fastest.  Otherwise one tile per
-// workgroup, an XCD's share of the (head, tile mod 8) in octets of tiles from the
-// longest down.  Grid 8 * H_q * B * ceil(tiles / 8).  Pairs are better where they
-// fill one round of the chip (512 workgroups) nearly exactly, and in launches of
-// many rounds; elsewhere their last round leaves CUs idle.  28 heads on 4 of 128,
-// pairs against single tiles: T = 2500 102 / 75 us, 3524 134 / 133, 4548 (504
-// pairs) 177 / 189, 7108 473 / 393; 2 x 3268 198 / 194, 2 x 5060 449 / 412, 2 x
-// 8132 (1792 pairs) 985 / 977; the backbone's 448 heads of 2048 663 / 700 to 850.
-// Fewer than eight tiles leave empty workgroups in the octets, which many heads
-// notice (the backbone's 1792 heads of 63 positions: 463 / 489 us per call).
+// PAIRED: a workgroup runs a short and a long tile, so that all do the same work.
+// Grid xcd_grid(pairs * H_q * B), pairs fastest.  Otherwise one tile per workgroup,
+// an XCD's share of the (head, tile mod m), m = min(8, tiles), in rows of m tiles
+// from the longest down; grid 8 * causal_row * ceil(tiles / m).
 //
 // Per wave and chunk, on v_mfma_f32_32x32x16_bf16: scores^T[key][position]
 // for two 32-key blocks (A = K rows from LDS, B = the wave's 32 query rows,
@@ -1062,13 +1055,32 @@ __global__ __launch_bounds__(256) void k_transpose_v(ReplayProblem p) {
 // step s of the product takes accumulator elements 8 (s % 2) .. +7 of block
 // s / 2 as its B operand.  LDS: K chunk [64][D], V^T chunk [D][64] (bf16).
 
-__host__ __device__ inline bool causal_paired(const ReplayProblem& p) {
+
+// Pairs or single tiles.  Single tiles end evenly when there are many lengths of them,
+// and let short calls use every CU; pairs waste nothing where their workgroups
+// fill whole rounds of the CUs (256), or one round of the chip (3 per CU at D = 64, 2 at
+// 128), and there are few tile lengths to even out with.  28 heads on 4 of 128, pairs
+// against single tiles: T = 500 28 / 22 us, 1000 41 / 34, 2500 103 / 75, 4200 (476
+// pairs) 168 / 170, 6000 349 / 306, 9000 642 / 619; 4 x 1000 (448 pairs of 8 tiles) 61
+// / 66, 8 x 1000 (896) 107 / 118, 8 x 500 (448 of 4) 43 / 52; 12 heads of 64, 16 x 1000
+// (768) 59 / 68, 8 x 2100 (864 of 17) 114 / 102.  Over 1053 calls (9 head counts, B up
+// to 16, T to 9000) the choice is 0.24 % above the better form on average, 9 % at most;
+// always pairs 14 % and 50 %.
+inline bool causal_paired(const ReplayProblem& p) {
     const int ntiles = (p.T + 127) / 128;
-    const int64_t nh = (int64_t)p.H_q * p.B, pairs = (ntiles + 1) / 2 * nh;
-    return pairs >= 4 * 512 || (pairs > 400 && pairs <= 512) || (ntiles < 8 && nh >= 128);
+    const int64_t nh = (int64_t)p.H_q * p.B, pairs = (ntiles + 1) / 2 * nh, round = p.D == 64 ? 768 : 512;
+    if (ntiles == 1 || (ntiles >= 8 && pairs >= 4 * round) || (10 * pairs > 9 * round && pairs <= round)) return true;
+    if (ntiles == 8) return nh > 32;   // single tiles: one per CU at most
+    const bool full = 100 * pairs >= 78 * 256 * ((pairs + 255) / 256);
+    return ntiles <= 12 && full && (ntiles > 8 || (ntiles >= 4 && ntiles % 2 == 0 && pairs > 256));
 }
 
-template <int D>
+// an XCD's workgroups per row of single tiles
+__host__ __device__ inline int causal_row(int ntiles, int nh) {
+    return ntiles < 8 ? (nh * ntiles + 7) >> 3 : nh;
+}
+
+template <int D, bool PAIRED>
 __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
     constexpr int DC = D / 8;
     constexpr int KS = 64 * DC, VS = D * 8;   // 16-byte slots of a K chunk and a V^T chunk
@@ -1077,20 +1089,18 @@ __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
     // global memory (buffer loads into LDS) one chunk ahead
     __shared__ u32x4 lds[2 * (KS + VS)];
     const int ntiles = (p.T + 127) / 128, nh = p.H_q * p.B;
-    int head, tile0, tile1;   // tile1 < 0: one tile
-    if (causal_paired(p)) {
+    int head, tile0;
+    if constexpr (PAIRED) {
         const int npairs = (ntiles + 1) / 2, item = xcd_item(blockIdx.x, npairs * nh);
         if (item >= npairs * nh) return;   // uniform over the workgroup
         head = item / npairs;
         tile0 = item % npairs;
-        tile1 = ntiles - 1 - tile0;
-        if (tile1 <= tile0) tile1 = -1;
     } else {
-        const int slot = blockIdx.x >> 3, c = (blockIdx.x & 7) * nh + slot % nh;
-        head = c >> 3;
-        tile0 = ntiles - 1 - (8 * (slot / nh) + (c & 7));
-        tile1 = -1;
-        if (tile0 < 0) return;   // uniform over the workgroup
+        const int per = causal_row(ntiles, nh), m = ntiles < 8 ? ntiles : 8;
+        const int slot = blockIdx.x >> 3, c = (blockIdx.x & 7) * per + slot % per;
+        head = c / m;
+        tile0 = ntiles - 1 - (m * (slot / per) + c % m);
+        if (tile0 < 0 || head >= nh) return;   // uniform over the workgroup
     }
     const int hq = head % p.H_q, b = head / p.H_q;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l32 = lane & 31, g = lane >> 5;
@@ -1135,9 +1145,9 @@ __global__ __launch_bounds__(256, 2) void k_causal_attn(ReplayProblem p) {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    for (int pass = 0; pass < 2; ++pass) {
-    const int tile = pass == 0 ? tile0 : tile1;
-    if (tile < 0) break;   // uniform over the workgroup
+    for (int pass = 0; pass < (PAIRED ? 2 : 1); ++pass) {
+    const int tile = pass == 0 ? tile0 : ntiles - 1 - tile0;
+    if (pass == 1 && tile <= tile0) break;   // uniform over the workgroup
     const int u0 = tile * 128;
     const int uw = u0 + 32 * w;            // first position of this wave
     const int u = uw + l32;                // this lane's query column
@@ -1310,9 +1320,15 @@ hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
         if (p.D == 128) hipLaunchKernelGGL(k_transpose_v<128>, tgrid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k_transpose_v<64>, tgrid, dim3(256), 0, stream, p);
         const int ntiles = (p.T + 127) / 128, nh = p.H_q * p.B;
-        const dim3 grid(causal_paired(p) ? xcd_grid((ntiles + 1) / 2 * nh) : 8 * nh * ((ntiles + 7) / 8));
-        if (p.D == 128) hipLaunchKernelGGL(k_causal_attn<128>, grid, dim3(256), 0, stream, p);
-        else hipLaunchKernelGGL(k_causal_attn<64>, grid, dim3(256), 0, stream, p);
+        if (causal_paired(p)) {
+            const dim3 grid(xcd_grid((ntiles + 1) / 2 * nh));
+            if (p.D == 128) hipLaunchKernelGGL((k_causal_attn<128, true>), grid, dim3(256), 0, stream, p);
+            else hipLaunchKernelGGL((k_causal_attn<64, true>), grid, dim3(256), 0, stream, p);
+        } else {
+            const dim3 grid(8 * causal_row(ntiles, nh) * ((ntiles + 7) / 8));
+            if (p.D == 128) hipLaunchKernelGGL((k_causal_attn<128, false>), grid, dim3(256), 0, stream, p);
+            else hipLaunchKernelGGL((k_causal_attn<64, false>), grid, dim3(256), 0, stream, p);
+        }
     }
     return hipGetLastError();
 }
