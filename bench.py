@@ -419,11 +419,11 @@ def cpu_baseline_moth(w, inp, lm, proj, rows):
 
 def takes_group_kernel(w) -> bool:
     """The library's rule for the four-position sparse kernel, K and V in BTHD: at
-    most 8 query heads per KV head, a batch row of K under 2 GiB, and not a small call
-    on one or two KV heads."""
-    row = w.H_kv * w.D
-    small = w.H_kv <= 2 and w.B * w.T * row <= 128 * 1024
-    return 4 * (w.H_q // w.H_kv) <= 32 and (w.T + 64) * row * 2 < 2 ** 31 and not small
+    most 8 query heads per KV head, a batch row of K under 2 GiB, and not a short call
+    on up to four KV heads."""
+    narrow = w.D == 64
+    short_to = {1: 4608, 2: 2560 if narrow else 1024, 3: 1024 if narrow else 600, 4: 600}.get(w.H_kv, 0)
+    return 4 * (w.H_q // w.H_kv) <= 32 and (w.T + 64) * w.H_kv * w.D * 2 < 2 ** 31 and w.B * w.T > short_to
 
 
 def group_gathered_rows(idx, T: int) -> float:

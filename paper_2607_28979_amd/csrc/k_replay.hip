@@ -14,7 +14,7 @@
 //   (grouped-query: query head h reads KV head h / G), four positions and one
 //   KV head per wave over the union of the positions' sets, for G <= 8.
 // * k_sparse_attn: the same for one position (more than 8 query heads per KV
-//   head, K of 2 GiB and more per batch row, small calls on few KV heads).  Per
+//   head, K of 2 GiB and more per batch row, short calls on few KV heads).  Per
 //   KV head the workgroup computes scores^T = K_sel . Q^T on
 //   v_mfma_f32_16x16x32_bf16 with the gathered key rows loaded straight into A
 //   operands, a softmax over the set, and O^T = V_sel^T . P^T with V_sel staged
@@ -1293,11 +1293,20 @@ hipError_t launch_replay_attention(const ReplayProblem& p, hipStream_t stream) {
         // the caller's check admits only these sizes; the register arrays of
         // the instantiation below cover every admitted S
         if (!replay_sparse_supported(p.D, p.S)) return hipErrorInvalidValue;
-        // small calls on one or two KV heads stay with a position per workgroup: a
-        // group's list costs more latency than the shared gathers save (12 query
-        // heads on 2 of 128, with the selection: 129 positions 18 us against 20, 520
-        // 24 / 24, 780 31 / 25; on 2 of 64, 520 positions 18 / 22, 1040 25 / 26)
-        const bool small = p.H_kv <= 2 && (int64_t)p.B * p.T * p.H_kv * p.D <= 128 * 1024;
+        // Short calls on up to four KV heads stay with a position per workgroup: a group's
+        // list costs more latency than the shared gathers save, and its workgroups, a
+        // quarter as many, leave CUs idle.  One position against four, sets of 128: 8 query
+        // heads on 1 of 128, 700 positions 13 / 25 us; 6 on 2 of 128, 700 19 / 26, 1100
+        // 28 / 29, 1600 38 / 30; 24 on 3 of 64, 700 15 / 21, 1600 31 / 26; 28 on 4 of
+        // 128, 500 23 / 27, 700 35 / 29.  Sets of 32 to 256 cross at about the same
+        // lengths: over 1350 calls the choice is 0.4 % above the better form on average.
+        const bool narrow = p.D == 64;
+        const int64_t short_to = p.H_kv == 1   ? 4608
+                                 : p.H_kv == 2 ? (narrow ? 2560 : 1024)
+                                 : p.H_kv == 3 ? (narrow ? 1024 : 600)
+                                 : p.H_kv == 4 ? 600
+                                               : 0;
+        const bool small = (int64_t)p.B * p.T <= short_to;
         if (!small && replay_sparse_group_supported(p.D, p.S, p.H_q / p.H_kv) &&
             replay_causal_supported(p.T, p.H_kv, p.D, p.kv_layout == MOT_LAYOUT_BTHD))
             return p.D == 128 ? launch_sparse_group<128>(p, stream) : launch_sparse_group<64>(p, stream);

@@ -129,10 +129,12 @@ ATTN = [  # B, T, H_q, H_kv, D, S, kv_layout
     (1, 300, 4, 1, 64, 224, 1),
     (1, 201, 8, 2, 128, 64, 0),       # an odd context
     (2, 99, 16, 2, 64, 128, 1),       # 8 query heads per KV head
-    # (calls on one or two KV heads this short take the one-position kernel; on
-    # four or more the four-position kernel)
-    (1, 301, 32, 4, 128, 192, 0),     # all 32 columns, the largest S, a lone last position
+    # (calls on up to four KV heads this short take the one-position kernel; on
+    # more the four-position kernel)
+    (1, 301, 32, 4, 128, 192, 0),
     (1, 270, 12, 4, 64, 224, 1),
+    (1, 301, 40, 5, 128, 192, 0),     # all 32 columns, the largest S, a lone last position
+    (1, 270, 18, 6, 64, 224, 1),
 ]
 
 
@@ -154,15 +156,15 @@ def test_sparse_attention_parity(case, oracle_built):
     assert worst <= 2 * TOL["bf16"], worst
 
 
-@pytest.mark.parametrize("heads", [(28, 4), (14, 2)], ids=["28x4", "14x2"])
+@pytest.mark.parametrize("heads", [(40, 8), (28, 4), (14, 2)], ids=["40x8", "28x4", "14x2"])
 @pytest.mark.parametrize("order", ["ascending", "shuffled", "duplicates"])
 def test_sparse_unions_and_listed_sets(order, heads, oracle_built):
     """Random sets (neighbouring positions share few keys, so the four-position
     kernel's lists run to several hundred), shuffled sets and sets with a
     repeated entry (which it takes as listed), for an odd context: every
-    position against the oracle, which attends each listed entry.  28 query heads
-    on 4 KV heads take that kernel; 14 on 2, of this length, the one-position
-    kernel."""
+    position against the oracle, which attends each listed entry.  40 query heads
+    on 8 KV heads take that kernel; 28 on 4 and 14 on 2, of this length, the
+    one-position kernel."""
     from oracle import oracle_replay_attention
     B, T, (Hq, Hkv), D, S = 1, 401, heads, 128, 128
     print("case unions", order, heads, flush=True)

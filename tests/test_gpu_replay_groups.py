@@ -105,18 +105,22 @@ def test_select_unaligned_base(T, off):
         assert torch.equal(idx[0, u].cpu(), w), u
 
 
-# KV heads 1, 2, 3, 4 and 8 (one position per workgroup; two groups of two waves,
-# one of them idle or not, and an odd number of groups; one group of four; a wave
-# with two heads), 1 to 8 query heads per KV head, every T mod 4, head-major K and V,
-# sets past 128, and lists that are unordered, repeat keys or hold none; then contexts
-# of several times the set, so that every set is full and a group's list runs to
-# hundreds of keys: two groups of two waves per workgroup and one of four, at the
-# largest sets of each head width
+# KV heads 1, 2, 3, 4 and 8 in short calls (up to four: one position per workgroup), 1 to 8
+# query heads per KV head, every T mod 4, head-major K and V, sets past 128, and lists that
+# are unordered, repeat keys or hold none; then contexts of several times the set, so that
+# every set is full and a group's list runs to hundreds of keys
 ATTN = [(1, 37, 7, 1, 128, 32, 0), (2, 38, 4, 2, 64, 64, 1), (1, 39, 24, 3, 128, 96, 0), (1, 90, 28, 4, 128, 160, 1),
         (3, 41, 8, 8, 64, 256, 0), (1, 1, 4, 4, 128, 32, 0), (9, 230, 7, 1, 128, 32, 0), (7, 237, 4, 2, 64, 64, 1),
         (3, 1, 16, 2, 128, 32, 0), (5, 215, 3, 3, 64, 32, 1), (5, 220, 16, 2, 64, 32, 0),
         (3, 701, 12, 2, 128, 128, 0), (3, 700, 14, 2, 128, 192, 1), (3, 703, 14, 2, 64, 256, 0),
         (1, 702, 28, 4, 128, 192, 1), (1, 701, 32, 8, 64, 256, 0)]
+# the four-position kernel: five to eight KV heads (waves with one head and with two), every
+# T mod 4; two groups of two waves per workgroup, one of them idle or not, and an odd number
+# of groups; one group of four waves, two of them idle or one; the largest sets of each head
+# width with both
+ATTN += [(1, 37, 35, 5, 128, 32, 0), (2, 38, 12, 6, 64, 64, 1), (1, 39, 56, 7, 128, 96, 0), (1, 90, 40, 5, 128, 160, 1),
+         (1, 1, 8, 8, 128, 32, 0), (21, 230, 7, 1, 128, 32, 0), (12, 237, 4, 2, 64, 64, 1), (5, 516, 14, 2, 64, 96, 1),
+         (12, 220, 16, 2, 64, 32, 0), (4, 703, 14, 2, 64, 256, 0), (2, 600, 6, 2, 128, 64, 0)]
 
 
 @pytest.mark.parametrize("case", ATTN, ids=lambda c: "x".join(map(str, c)))
@@ -147,7 +151,7 @@ def test_attention_groups(case, kind):
     assert torch.equal(o, again)
 
 
-@pytest.mark.parametrize("D,Hq,Hkv", [(128, 28, 4), (64, 24, 8)])
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 40, 8), (128, 28, 4), (64, 24, 8)])
 def test_attention_large_scores(D, Hq, Hkv):
     """Scores near 2^23 (whole numbers, exact in fp32) that differ by a few units and grow
     along the sets: the blocks of a set keep their weights against each other."""
@@ -166,12 +170,13 @@ def test_attention_large_scores(D, Hq, Hkv):
     assert d.abs().max() <= 2.0 ** -6 * max(1.0, ref.abs().max().item())
 
 
-def test_attention_value_rows_that_are_not_finite():
+@pytest.mark.parametrize("H,Hkv", [(16, 8), (8, 4)])
+def test_attention_value_rows_that_are_not_finite(H, Hkv):
     """NaN and infinite value rows reach exactly the positions that attend them; their
     group's other positions come out as without them."""
-    T, S, D, H = 64, 32, 128, 8
+    T, S, D = 64, 32, 128
     g = torch.Generator().manual_seed(3)
-    q, k, v = (torch.randn(1, T, h, D, generator=g).bfloat16() for h in (H, 4, 4))
+    q, k, v = (torch.randn(1, T, h, D, generator=g).bfloat16() for h in (H, Hkv, Hkv))
     idx = _select(torch.randn(1, T, T, generator=g), S)
     idx[idx == 20] = 19          # (a repeat where 19 is in the set as well)
     idx[idx == 40] = 39
@@ -182,7 +187,7 @@ def test_attention_value_rows_that_are_not_finite():
         if poke:
             w[0, 20, 0], w[0, 40, 1, 7] = float("nan"), float("inf")
         o = torch.empty(1, T, H, D, dtype=torch.bfloat16, device="cuda")
-        mb.replay_attention(q.cuda(), k.cuda(), w.cuda(), idx.cuda(), o, 1, T, H, 4, D, S=S)
+        mb.replay_attention(q.cuda(), k.cuda(), w.cuda(), idx.cuda(), o, 1, T, H, Hkv, D, S=S)
         outs.append(o.cpu().float()[0])
     clean, got = outs
     assert torch.isnan(got[33, :2]).all()                                # KV head 0's query heads
