@@ -239,3 +239,21 @@ def test_capture_begun_outside_torch():
         assert all(torch.equal(a, b) for a, b in zip(out, want))
         _translate(w, d)
     assert hip.hipGraphExecDestroy(ex) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("workload", [1, 3, 4])
+@pytest.mark.parametrize("top_k", [0, 1])
+def test_rows_of_short_tiles(workload, top_k):
+    """A tile's last rows, at every remainder of the groups of eight that it stores: the
+    bits they have in a longer call (a routed tile holds other rows there)."""
+    import torch
+    w = small_variant(WORKLOADS[workload], L_src=2, L_tgt=2, B=1, T=260)
+    w = w.with_(top_k=top_k or w.E)
+    d = {n: to_dev(getattr(generate(w), n), w.dtype) for n in ("src_k", "src_v", "w1", "b1", "w2", "b2", "wr", "br")}
+    long = _translate(w, d, scratch=False)
+    for T in (1, 2, 7, 8, 9, 15, 17, 31, 33, 95, 96, 97, 127, 129, 200):
+        print("case", workload, top_k, T, flush=True)
+        sub = dict(d, src_k=d["src_k"][:, :, :T].contiguous(), src_v=d["src_v"][:, :, :T].contiguous())
+        for a, b in zip(long, _translate(w.with_(T=T), sub, scratch=False)):
+            assert torch.equal(a[:, :, :T], b)
