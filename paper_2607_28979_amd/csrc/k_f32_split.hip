@@ -31,7 +31,7 @@
 // c ^ ((r >> 2) & 3) (16 lanes reading one chunk of 16 rows touch 16 distinct
 // bank groups).
 //
-// Bound: latency at one token tile (64 tokens: 84.8 -> 46.8 us per call against
+// Bound: latency at one token tile (64 tokens: 84.8 -> 45.6 us per call against
 // v_mfma_f32_16x16x4_f32 with operands straight from global memory; 42.5 with six
 // products), the sum of splitting, LDS and MFMA issue at many (999 tokens: 698 ->
 // 318 us, 119 TFLOP/s of fp32 products; 266 with six products and without the row
@@ -103,6 +103,12 @@ struct Acc {
     float big[T::IA + T::IB];   // largest magnitude this thread split of item q's row
 };
 
+// v of another lane of the quad
+template <int CTRL>
+__device__ __forceinline__ float quad_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
 // Row maxima of a tile (TM rows of A, then TN of B) from the threads' shares; ends
 // in a barrier
 template <class T>
@@ -110,8 +116,8 @@ __device__ __forceinline__ void row_maxima(const Acc<T>& acc, float* s_max) {
 #pragma unroll
     for (int q = 0; q < T::IA + T::IB; ++q) {
         float v = acc.big[q];
-        v = fmaxf(v, __shfl_xor(v, 1, 64));
-        v = fmaxf(v, __shfl_xor(v, 2, 64));
+        v = fmaxf(v, quad_swap<0xB1>(v));   // lane ^ 1
+        v = fmaxf(v, quad_swap<0x4E>(v));   // lane ^ 2
         const int row = (q < T::IA ? 0 : T::TM) + (threadIdx.x >> 2) + 64 * (q < T::IA ? q : q - T::IA);
         if ((threadIdx.x & 3) == 0) s_max[row] = v;
     }
@@ -273,10 +279,15 @@ __device__ __forceinline__ f32x16 finish_block(const f32x16& hi, const f32x16& l
     f32x16 v;
     bool bad = false;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        v[e] = hi[e] + lo[e];
-        const float rm = row_max[8 * (e >> 2) + 4 * g + (e & 3)], mag = fabsf(v[e]);
-        bad |= !(mag <= 3.402823466e38f) || (mag < least * (1.0f + rm + col_max) && rm > 0.f && col_max > 0.f);
+    for (int i = 0; i < 4; ++i) {
+        const f32x4 rm = ld4(row_max + 8 * i + 4 * g);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = 4 * i + r;
+            v[e] = hi[e] + lo[e];
+            const float mag = fabsf(v[e]);
+            bad |= !(mag <= 3.402823466e38f) || (mag < least * (1.0f + rm[r] + col_max) && rm[r] > 0.f && col_max > 0.f);
+        }
     }
     if (__any(bad)) {
 #pragma unroll
@@ -375,7 +386,7 @@ __device__ __forceinline__ void router_tile(const Problem& p, uint32_t code, int
 template <class T, bool GENERAL>
 __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab ut) {
     __shared__ u32x4 s_lds[T::LDS];
-    __shared__ float s_max[T::TM + T::TN];
+    __shared__ __align__(16) float s_max[T::TM + T::TN];
     static_assert(T::LDS >= 4 * 64 * 4, "the router's partial logits fit");
     const int EH = p.E * p.hidden, nA = (EH + T::TM - 1) / T::TM, d_in = p.d_in;
     const int nr = (p.n_tok + 63) / 64, per = nr + nA * ((p.n_tok + T::TN - 1) / T::TN);
@@ -479,7 +490,7 @@ __global__ __launch_bounds__(256, 3) void k_f32_split_gemm1(Problem p, UnitTab u
 template <class T>
 __global__ __launch_bounds__(256, 3) void k_f32_split_gemm2(Problem p, UnitTab ut) {
     __shared__ u32x4 s_lds[T::LDS];
-    __shared__ float s_max[T::TM + T::TN];
+    __shared__ __align__(16) float s_max[T::TM + T::TN];
     const int E = p.E, hidden = p.hidden, EH = E * hidden, d_out = p.d_out, nA = (d_out + T::TM - 1) / T::TM;
     const int per = nA * ((p.n_tok + T::TN - 1) / T::TN), item = xcd_item(ut.n * per);
     if (item >= ut.n * per) return;   // uniform over the workgroup
