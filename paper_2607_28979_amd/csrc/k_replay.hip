@@ -153,7 +153,7 @@ struct RowKeys {
 // cycles, the vector ALUs are 39 % busy).  8192 rows of a causal map, sets of 128: 119
 // us with the row's keys in LDS (4 workgroups per CU, every key counted by an LDS
 // atomic), 55 us with them in registers and one key in ten counted (6 waves per SIMD
-// spill 8 registers: 55 MB of writes beside the 4 MB of sets).
+// spill 8 registers: 65 MB of writes beside the 4 MB of sets).
 //
 // grid (T, B), 256 threads; dynamic LDS: per-chunk counts s_gt, s_eq
 // (T / (64 Q) + 4 each)
